@@ -1,0 +1,70 @@
+"""The device sort and scans behind the binning, at the sizes where they
+change form: the edge list against a stable host sort, the bucket offsets
+against direct counts."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2101_05031_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def lattice(n, dtype, seed):
+    """n short struts with few distinct lower z (long runs of equal keys),
+    of both signs."""
+    rng = np.random.default_rng(seed)
+    a = rng.uniform(-20.0, 20.0, size=(n, 3))
+    a[:, 2] = rng.integers(-40, 40, size=n) * 0.37
+    d = rng.uniform(0.2, 1.0, size=(n, 3))
+    nodes = np.concatenate([a, a + d]).astype(dtype)
+    edges = np.stack([np.arange(n), np.arange(n) + n], 1).astype(np.int32)
+    flip = rng.random(n) < 0.5
+    edges[flip] = edges[flip, ::-1]
+    return nodes, np.ascontiguousarray(edges), np.full(n, 0.5, dtype)
+
+
+# one block (up to 8192 items), a tile of 2048, the histogram summed by every
+# block (up to 64 blocks, 131072 items) or scanned row by row
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 511, 513, 8191, 8192, 8193, 10241, 131071, 131072,
+                               131073, 200003])
+def test_edge_list_is_the_stable_sort(n, dtype):
+    nodes, edges, w = lattice(n, dtype, n)
+    grid = synth.Grid(-25.0, -25.0, 1.0, 1.0, 50, 50, -20.0, 0.5, 80)
+    t = [torch.from_numpy(x).cuda() for x in (nodes, edges, w)]
+    b = api.lattice_bin(*t, 0.5, 1.0, grid, tile=8, slab=4)
+    z = np.minimum(nodes[edges[:, 0], 2], nodes[edges[:, 1], 2])
+    assert b.info()["n_binned"] == n
+    assert np.array_equal(b.order().cpu().numpy(), np.argsort(z, kind="stable"))
+
+
+# bucket counts whose scan takes one block, one or several tiles per block sum
+@pytest.mark.parametrize("W,H,planes", [(16, 16, 8), (511, 129, 8), (1024, 1024, 8),
+                                        (1024, 1030, 37)])
+def test_bucket_offsets_count_the_pairs(W, H, planes):
+    nodes, edges, w = lattice(3000, np.float32, 5)
+    grid = synth.Grid(-25.0, -25.0, 50.0 / W, 50.0 / H, W, H, -20.0, 40.0 / planes, planes)
+    t = [torch.from_numpy(x).cuda() for x in (nodes, edges, w)]
+    b = api.lattice_bin(*t, 0.5, 1.0, grid, tile=8, slab=1)
+    off, ids = b.export(0)
+    off, ids = off.cpu().numpy(), ids.cpu().numpy()
+    assert off[0] == 0 and off[-1] == len(ids) and (np.diff(off) >= 0).all()
+    # each strut's box, evaluated as the ABI states it
+    info = b.info()
+    cnt = np.zeros((planes + 1, info["tiles_y"] + 1, info["tiles_x"] + 1), np.int64)
+    a, c = nodes[edges[:, 0]].astype(np.float64), nodes[edges[:, 1]].astype(np.float64)
+    o = np.array([grid.x0, grid.y0, grid.z0])
+    inv = 1.0 / np.array([grid.dx, grid.dy, grid.dz])
+    n = np.array([W, H, planes])
+    i0 = np.floor(((np.minimum(a, c) - 0.5) - o) * inv - 0.5)
+    i1 = np.ceil(((np.maximum(a, c) + 0.5) - o) * inv - 0.5)
+    ok = ((i1 >= 0) & (i0 <= n - 1)).all(1)
+    i0 = (np.clip(i0, 0, n - 1).astype(int) // [8, 8, 1])[ok]
+    i1 = (np.clip(i1, 0, n - 1).astype(int) // [8, 8, 1])[ok]
+    for corner in range(8):                       # 3-d difference array of the boxes
+        s = [(corner >> q) & 1 for q in range(3)]
+        p = [np.where(s[q], i1[:, q] + 1, i0[:, q]) for q in range(3)]
+        np.add.at(cnt, (p[2], p[1], p[0]), (-1) ** sum(s))
+    cnt = cnt.cumsum(0).cumsum(1).cumsum(2)[:planes, :info["tiles_y"], :info["tiles_x"]]
+    assert np.array_equal(np.diff(off), cnt.reshape(-1))
