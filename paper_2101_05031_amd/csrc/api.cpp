@@ -1273,7 +1273,7 @@ lsl_status slice_polylines(const lattice_bins* cb, int32_t nk, const void* field
     for (int32_t k = 0; k < nk; ++k) longest = std::max<int64_t>(longest, h_off[k + 1] - h_off[k]);
     int32_t rounds = 1;
     while (((int64_t)1 << (rounds - 1)) < longest) ++rounds;
-    LSL_TRY(b->grow(&b->pscratch, &b->pscratch_elems, polyline_scratch_elems((uint64_t)tot), st));
+    LSL_TRY(b->grow(&b->pscratch, &b->pscratch_elems, polyline_scratch_elems((uint64_t)tot, nk, b->grid.W, b->grid.H), st));
     return launch_polylines(img, field, b->dtype, b->C, nk, b->grid.W, b->grid.H, b->ctmp, offsets,
                             (uint64_t)tot, rounds, segs, b->pscratch, chain, rank, st);
 }

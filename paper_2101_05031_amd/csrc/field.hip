@@ -95,10 +95,19 @@ __global__ __launch_bounds__(256) void k_bits_blk(const T* field, int32_t nk, in
     const T* f = field + k * (uint64_t)W * (uint64_t)H;
     const int i = c * 64 + lane;
     uint64_t word = 0;                                     // lane b < 8: block c*8 + b
+    // all eight rows are read before the first is used, at clamped places (a
+    // load under a condition waits for its own value before the next one:
+    // 32 planes of 2048^2 173 -> 99 us, 3.1 -> 5.4 TB/s)
+    T v[8];
+    const int ic = i < W ? i : W - 1;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         const int j = by * 8 + r;
-        const uint64_t m = ballot64(i < W && j < H && f[(size_t)j * W + i] >= C);
+        v[r] = f[(size_t)(j < H ? j : H - 1) * W + ic];
+    }
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const uint64_t m = ballot64(i < W && by * 8 + r < H && v[r] >= C);
         word |= ((m >> (8 * (lane & 7))) & 0xffull) << (8 * r);
     }
     if (lane < 8 && c * 8 + lane < nbx) out[kb * (uint64_t)nbx + (uint64_t)(c * 8 + lane)] = word;

@@ -103,3 +103,39 @@ def test_polylines_capacity_and_repeatability():
     # without chains: the same segments
     s3, _, c3, r3 = api.slice_polylines(b, f, chains=False)
     assert c3 is None and torch.equal(s3.view(torch.int32), segs.view(torch.int32))
+
+
+def _stripes(H, W, period, sheared):
+    """Bars (walls of segments one list index apart per row) or a slope."""
+    j, i = np.mgrid[0:H, 0:W]
+    t = (i + (j // 3 if sheared else 0)) % (2 * period)
+    return np.where(t < period, 1.5, 0.5)
+
+
+@pytest.mark.parametrize("W,H,nk", [(2, 2, 1), (9, 7, 3), (64, 257, 2), (520, 131, 1)])
+@pytest.mark.parametrize("pattern", ["noise", "bars", "shear", "spiral", "ring"])
+def test_chains_of_every_shape(pattern, W, H, nk):
+    """Chains shorter and longer than the walk between two jump stations:
+    single-pixel loops and saddles, long open walls whose segments lie a
+    constant stride apart, one long spiral, a loop around the whole plane."""
+    rng = np.random.default_rng(W + H)
+    if pattern == "noise":
+        f = rng.uniform(0.0, 2.0, size=(nk, H, W))
+    elif pattern in ("bars", "shear"):
+        f = np.stack([_stripes(H, W, 3 + k, pattern == "shear") for k in range(nk)])
+    elif pattern == "spiral":
+        j, i = np.mgrid[0:H, 0:W]
+        x, y = i - W / 2.0, j - H / 2.0
+        f = np.stack([1.0 + np.sin(np.hypot(x, y) + np.arctan2(y, x) + k) for k in range(nk)])
+    else:
+        f = np.zeros((nk, H, W))
+        f[:, 1:-1, 1:-1] = 2.0
+    lat = synth.tiny_lattice("one", np.float32)
+    b = bin_lattice(lat, synth.grid_for(lat, max(W, 8), max(H, 8), nk, dz=0.1))
+    g = copy.copy(b.grid)
+    g.W, g.H = W, H
+    b = bin_lattice(lat, g)
+    field = torch.from_numpy(f.astype(np.float32)).cuda()
+    segs, off, chain, rank = api.slice_polylines(b, field)
+    if len(segs):
+        check_planes(lat, field, segs, off, chain, rank, pattern)
