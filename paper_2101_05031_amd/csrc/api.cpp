@@ -811,7 +811,11 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
     int which = 0;
     uint32_t* perm_src = vals;
     if (E > 0) {
-        if ((s = radix_sort_pairs(klo, vals, ka, va, E, 32, stmp, &which, st))) return fail(s);
+        // (float32: struts that are not binned have no key and drop out; a
+        // float64 key's low word may be anything)
+        if ((s = radix_sort_pairs(klo, vals, ka, va, E, 32, stmp, &which, st,
+                                  L->dtype == LSL_F32 && !L->support ? counters : nullptr)))
+            return fail(s);
         uint32_t* sv = which ? va : vals;
         if (L->dtype == LSL_F64) {
             uint32_t* sk = which ? ka : klo;        // low words, sorted (unused now)
@@ -1414,7 +1418,7 @@ BackArgs back_args(const lattice_bins* b, int g, int32_t k0, int32_t nk, int s_l
 // What decides the kernels a slab group's graphs record (the cached graphs
 // of one shape differ only in launch arguments).
 struct GraphShape {
-    int32_t dtype, kernel, strut_R, plane_ref, slab, tile, phase;
+    int32_t dtype, kernel, strut_R, plane_ref, slab, planes, tile, phase;
     int32_t field, bits, segs, slot;
 };
 
@@ -1465,7 +1469,7 @@ lsl_status batch_group_work(lattice_bins* b, int g, int32_t k0, int32_t nk, int 
         ba.queue = b->queue_in_alt ? qv2 : qv;
         ba.n_items = n_items;
         ba.counter = counter;
-        return launch_persistent(b->dtype, ba, persistent_blocks(b->dtype, b->slab), st);
+        return launch_persistent(b->dtype, ba, st);
     }
     LSL_TRY(launch_contours_count(img, nkg, b->grid.W, b->grid.H, offsets + (kg0 - k0), nullptr,
                                   b->ctmp, base, st));
@@ -1639,6 +1643,8 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
         // decides which kernels run) and which of the shape's two entries
         // this group takes
         if (!cap) LSL_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+        const int32_t planes = slab_planes(b->slab, std::min(k0 + nk, (s_hi + 1) * b->slab) -
+                                                        std::max(k0, s_lo * b->slab));
         hipGraph_t gr[3] = {nullptr, nullptr, nullptr};
         lsl_status cs = LSL_OK;
         for (int ph = 0; ph < 3 && cs == LSL_OK; ++ph)
@@ -1650,7 +1656,7 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
         if (cs == LSL_OK && hipEventRecord(ev[1], st) != hipSuccess) cs = LSL_EDEVICE;
         for (int ph = 0; ph < 3 && cs == LSL_OK; ++ph) {
             GraphShape shape{b->dtype,   b->kernel,        b->strut_R ? 1 : 0,
-                             b->plane_ref ? 1 : 0, b->slab, b->tile, ph,
+                             b->plane_ref ? 1 : 0, b->slab, planes, b->tile, ph,
                              field ? 1 : 0, bits ? 1 : 0, capacity > 0 ? 1 : 0,
                              (int32_t)((n_call_groups - 1) & 1)};
             std::vector<unsigned char> key((unsigned char*)&shape,

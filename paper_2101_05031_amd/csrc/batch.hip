@@ -36,11 +36,11 @@ __global__ void k_queue_keys(FieldArgs a, uint32_t n_items, uint32_t* keys, uint
     vals[it] = it;
 }
 
-template <typename T, int SZ, int K, bool SR, bool PR>
+template <typename T, int SZ, int K, bool SR, int FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_persistent(FieldArgs a, const uint32_t* queue,
                                                     uint32_t n_items, uint32_t* counter) {
     __shared__ uint32_t s_item;
-    const int wv = threadIdx.x >> 6;
+    const int wv = wave_index();
     const int nsub = a.tile / kBlockPix;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(counter, 1u);
@@ -53,10 +53,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
         t /= (uint32_t)a.ntx;
         const int ty = (int)(t % (uint32_t)a.nty);
         t /= (uint32_t)a.nty;
-        if constexpr (std::is_same<T, float>::value && K == LSL_KERNEL_QUARTIC && !PR) {
+        if constexpr (FORM != kFormBlock) {
             __shared__ q32::Lds<SZ> lds[4];
             for (int sub = wv; sub < nsub * nsub; sub += 4)
-                q32::field_block<SZ, false, SR>(a, a.s_lo + (int)t, tx, ty, sub, lds[wv]);
+                q32::field_block<SZ, false, SR, FORM == kFormAligned>(a, a.s_lo + (int)t, tx, ty,
+                                                                      sub, lds[wv]);
         } else {
             __shared__ Stage<T> stage[4][kWave];
             __shared__ T pend[4][fieldk::pend_elems<T, SZ>()];
@@ -68,68 +69,54 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     }
 }
 
-template <typename T, int SZ>
-int blocks_t() {
+// as many blocks as the GPU holds at once
+template <typename T, int SZ, int K, bool SR, int FORM>
+lsl_status persistent_t(const BatchArgs& b, hipStream_t st) {
     int dev = 0, cus = 0, per = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per, k_persistent<T, SZ, LSL_KERNEL_QUARTIC, false, false>, 256, 0) !=
-        hipSuccess)
-        return 0;
-    return cus * (per > 0 ? per : 1);
-}
-
-template <typename T>
-int blocks_dt(int slab) {
-    if (slab <= 1) return blocks_t<T, 1>();
-    if (slab <= 2) return blocks_t<T, 2>();
-    if (slab <= 4) return blocks_t<T, 4>();
-    if (slab <= 8) return blocks_t<T, 8>();
-    return blocks_t<T, 16>();
-}
-
-template <typename T, int K, bool SR, bool PR>
-lsl_status persistent_dtkp(const BatchArgs& b, int n_blocks, hipStream_t st) {
-    const int s = b.f.slab;
-    if (s <= 1)
-        k_persistent<T, 1, K, SR, PR><<<n_blocks, 256, 0, st>>>(b.f, b.queue, b.n_items, b.counter);
-    else if (s <= 2)
-        k_persistent<T, 2, K, SR, PR><<<n_blocks, 256, 0, st>>>(b.f, b.queue, b.n_items, b.counter);
-    else if (s <= 4)
-        k_persistent<T, 4, K, SR, PR><<<n_blocks, 256, 0, st>>>(b.f, b.queue, b.n_items, b.counter);
-    else if (s <= 8)
-        k_persistent<T, 8, K, SR, PR><<<n_blocks, 256, 0, st>>>(b.f, b.queue, b.n_items, b.counter);
-    else
-        k_persistent<T, 16, K, SR, PR><<<n_blocks, 256, 0, st>>>(b.f, b.queue, b.n_items,
-                                                                 b.counter);
+    LSL_HIP(hipGetDevice(&dev));
+    LSL_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    LSL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_persistent<T, SZ, K, SR, FORM>,
+                                                         256, 0));
+    const int n = cus * (per > 0 ? per : 1);
+    k_persistent<T, SZ, K, SR, FORM><<<n, 256, 0, st>>>(b.f, b.queue, b.n_items, b.counter);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }
 
-template <typename T, int K, bool SR>
-lsl_status persistent_dtk(const BatchArgs& b, int n_blocks, hipStream_t st) {
+template <typename T, int SZ, int K, bool SR>
+lsl_status persistent_form(const BatchArgs& b, hipStream_t st) {
     if constexpr (std::is_same<T, float>::value && K == LSL_KERNEL_QUARTIC) {
-        if (b.f.plane_ref) return persistent_dtkp<T, K, SR, true>(b, n_blocks, st);
+        if constexpr (SZ >= 8) {
+            if (field_form(b.f, SZ) == kFormAligned)
+                return persistent_t<T, SZ, K, SR, kFormAligned>(b, st);
+        }
+        if (field_form(b.f, SZ) != kFormBlock)
+            return persistent_t<T, SZ, K, SR, kFormGeneral>(b, st);
     }
-    return persistent_dtkp<T, K, SR, false>(b, n_blocks, st);
+    return persistent_t<T, SZ, K, SR, kFormBlock>(b, st);
+}
+
+template <typename T, int K, bool SR>
+lsl_status persistent_dtk(const BatchArgs& b, hipStream_t st) {
+    switch (slab_planes(b.f.slab, b.f.nk)) {
+        case 1: return persistent_form<T, 1, K, SR>(b, st);
+        case 2: return persistent_form<T, 2, K, SR>(b, st);
+        case 4: return persistent_form<T, 4, K, SR>(b, st);
+        case 8: return persistent_form<T, 8, K, SR>(b, st);
+        default: return persistent_form<T, 16, K, SR>(b, st);
+    }
 }
 
 template <typename T>
-lsl_status persistent_dt(const BatchArgs& b, int n_blocks, hipStream_t st) {
+lsl_status persistent_dt(const BatchArgs& b, hipStream_t st) {
     if (b.f.kernel == LSL_KERNEL_GAUSS)
-        return b.f.strut_R ? persistent_dtk<T, LSL_KERNEL_GAUSS, true>(b, n_blocks, st)
-                           : persistent_dtk<T, LSL_KERNEL_GAUSS, false>(b, n_blocks, st);
-    return b.f.strut_R ? persistent_dtk<T, LSL_KERNEL_QUARTIC, true>(b, n_blocks, st)
-                       : persistent_dtk<T, LSL_KERNEL_QUARTIC, false>(b, n_blocks, st);
+        return b.f.strut_R ? persistent_dtk<T, LSL_KERNEL_GAUSS, true>(b, st)
+                           : persistent_dtk<T, LSL_KERNEL_GAUSS, false>(b, st);
+    return b.f.strut_R ? persistent_dtk<T, LSL_KERNEL_QUARTIC, true>(b, st)
+                       : persistent_dtk<T, LSL_KERNEL_QUARTIC, false>(b, st);
 }
 
 }  // namespace
-
-int persistent_blocks(int dtype, int slab) {
-    return dtype == LSL_F32 ? blocks_dt<float>(slab) : blocks_dt<double>(slab);
-}
 
 lsl_status launch_queue_build(const FieldArgs& f, uint32_t* keys, uint32_t* vals,
                               uint32_t* keys_alt, uint32_t* vals_alt, uint32_t n_items,
@@ -142,11 +129,9 @@ lsl_status launch_queue_build(const FieldArgs& f, uint32_t* keys, uint32_t* vals
     return LSL_OK;
 }
 
-lsl_status launch_persistent(int dtype, const BatchArgs& b, int n_blocks, hipStream_t st) {
+lsl_status launch_persistent(int dtype, const BatchArgs& b, hipStream_t st) {
     if (b.n_items == 0) return LSL_OK;
-    if (n_blocks <= 0) n_blocks = 1024;
-    return dtype == LSL_F32 ? persistent_dt<float>(b, n_blocks, st)
-                            : persistent_dt<double>(b, n_blocks, st);
+    return dtype == LSL_F32 ? persistent_dt<float>(b, st) : persistent_dt<double>(b, st);
 }
 
 }  // namespace lsl

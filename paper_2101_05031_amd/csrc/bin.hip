@@ -108,21 +108,26 @@ __global__ void k_pair_counts(const uint32_t* active, uint32_t n, const SRange* 
     if (a == n) counts[a] = rcounts[a] = 0u;
 }
 
-// One wave emits the cells of 64 active struts, one strut at a time, the
+// One wave emits the cells of PER active struts, one strut at a time, the
 // wave's lanes writing consecutive items (coalesced stores): (cell key
 // ((slab - sa) nty + ty) nseg + column segment, the strut's edge-list
-// position), slab-major, then tile row, then segment.
+// position), slab-major, then tile row, then segment.  64 struts per wave
+// make the fewest loads; with fewer than kEmitFew active struts that leaves
+// the GPU idle behind a few long chains, and a wave takes 4 (EMIT_MEASURED).
+constexpr uint32_t kEmitFew = 65536;
+
+template <int PER>
 __global__ __launch_bounds__(256) void k_cell_emit(const uint32_t* active, uint32_t n,
                                                    const SRange* rg, int32_t sa, int32_t nty,
                                                    int32_t nseg, const uint32_t* toff,
                                                    uint32_t* keys, uint32_t* vals, uint32_t cap) {
     const int lane = lane_id();
-    const uint32_t a0 = (blockIdx.x * blockDim.x + threadIdx.x) & ~63u;
+    const uint32_t a0 = ((blockIdx.x * blockDim.x + threadIdx.x) / kWave) * PER;
     if (a0 >= n) return;
     const uint32_t a = a0 + lane;
     SRange r{0, 0, 0, 0, 0, -1};
     uint32_t off = 0, pos = 0, cnt = 0;
-    if (a < n) {
+    if (lane < PER && a < n) {
         pos = active[a];
         r = rg[pos];
         off = toff[a];
@@ -132,7 +137,7 @@ __global__ __launch_bounds__(256) void k_cell_emit(const uint32_t* active, uint3
     const uint32_t ny = (uint32_t)(r.ty1 - r.ty0 + 1);
     const uint32_t xs0 = (uint32_t)r.tx0 / kSegTiles;
     const uint32_t nxs = (uint32_t)r.tx1 / kSegTiles - xs0 + 1;
-    const int m = (n - a0) < 64u ? (int)(n - a0) : 64;
+    const int m = (n - a0) < (uint32_t)PER ? (int)(n - a0) : PER;
     for (int s = 0; s < m; ++s) {
         const uint32_t c = __shfl(cnt, s, kWave);
         const uint32_t o = __shfl(off, s, kWave);
@@ -303,9 +308,14 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
     const uint32_t n_cells = (uint32_t)(g.sb - g.sa + 1) * (uint32_t)g.nty * nseg;
     if (g.n_pairs > 0 && g.n_cells > 0) {
         // 3. emit (cell, strut position) items in edge-list order
-        const unsigned ge = (unsigned)(((size_t)g.n_active + 255) / 256);
-        k_cell_emit<<<ge, 256, 0, st>>>(g.active, g.n_active, g.ranges, g.sa, g.nty, (int32_t)nseg,
-                                        g.toff, g.k0, g.v0, g.n_cells);
+        if (g.n_active < kEmitFew)
+            k_cell_emit<4><<<(g.n_active + 15) / 16, 256, 0, st>>>(
+                g.active, g.n_active, g.ranges, g.sa, g.nty, (int32_t)nseg, g.toff, g.k0, g.v0,
+                g.n_cells);
+        else
+            k_cell_emit<16><<<(unsigned)(((size_t)g.n_active + 63) / 64), 256, 0, st>>>(
+                g.active, g.n_active, g.ranges, g.sa, g.nty, (int32_t)nseg, g.toff, g.k0, g.v0,
+                g.n_cells);
         LSL_HIP(hipGetLastError());
         // 4. stable sort by cell, and the cells' CSR
         int which = 0;

@@ -78,6 +78,11 @@ __device__ __forceinline__ Line strut_line(const StrutRec<T>& r) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
+// the wave's index in its block, in a scalar register
+__device__ __forceinline__ int wave_index() {
+    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+}
+
 __device__ __forceinline__ uint64_t lanes_below(int lane) {
     return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
@@ -128,11 +133,15 @@ lsl_status exclusive_scan_u64(const uint64_t* in, uint64_t* out, size_t n,
 // Stable LSD radix sort of (key, value) pairs on key bits [0, key_bits).
 // Input in (k0, v0); (k1, v1) are equal-sized alternates.  Returns in *which
 // 0 if the result is in (k0, v0), 1 if in (k1, v1).  tmp must hold
-// radix_tmp_elems(n) uint32 elements.
+// radix_tmp_elems(n) uint32 elements.  With n_keep (device, the number of
+// keys other than kNoKey, which no item sorts before) only the first *n_keep
+// places of the result are the sorted items with a key; what follows is
+// unspecified, and the passes after the first move *n_keep items instead of n.
+constexpr uint32_t kNoKey = 0xffffffffu;
 size_t radix_tmp_elems(size_t n);
 lsl_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
                             size_t n, int key_bits, uint32_t* tmp, int* which,
-                            hipStream_t st);
+                            hipStream_t st, const uint32_t* n_keep = nullptr);
 
 lsl_status fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 lsl_status fill_bytes0(void* p, size_t bytes, hipStream_t st);

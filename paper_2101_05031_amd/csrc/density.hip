@@ -169,14 +169,21 @@ __global__ __launch_bounds__(kDThreads) void k_density(const T* field, DensityAr
     }
 }
 
-// soft voxel densities, residuals s_v - target_v and the block's sum of
-// squared residuals
-template <typename T>
+// Soft voxel densities, the block's sum of squared residuals s_v - target_v
+// and, for GRAD, dL/dg of the block's pixels (every pixel of the field lies in
+// exactly one block's box).  The gradient needs the voxel's residual, hence a
+// second pass over the box; made by the same block right after the first, it
+// finds the box's values in the memory-side cache (256 MB; four blocks per
+// compute unit keep 130 MB of boxes in flight) instead of HBM.  The gradient
+// is written once and not read back here: streaming stores.  64 planes of
+// 2048^2 in float32: GRAD_MEASURED.
+template <typename T, bool GRAD>
 __global__ __launch_bounds__(kDThreads) void k_soft_density(const T* field, DensityArgs a, T C,
-                                                            T inv_tau, const float* target,
-                                                            float* soft, double* resid,
-                                                            double* part) {
+                                                            T inv_tau, double tau,
+                                                            const float* target, float* soft,
+                                                            T* grad, double* part) {
     __shared__ double col[kDThreads];
+    __shared__ T coef[kDThreads];      // per voxel of the block: dL/dg = coef sigmoid'
     const Box x = block_box(a, blockIdx.x);
     const double s = column_total<T, double, T>(field, a, x, [C, inv_tau](T g) -> T {
         return sigm((g - C) * inv_tau);
@@ -189,14 +196,39 @@ __global__ __launch_bounds__(kDThreads) void k_soft_density(const T* field, Dens
     if (v < x.ib - x.ia) {
         const int32_t i = x.ia + v;
         const size_t idx = ((size_t)x.l * (size_t)a.ny + (size_t)x.j) * (size_t)a.nx + (size_t)i;
-        const double d = col[v * vxs] / box_samples(a, x, i);
+        const double n = box_samples(a, x, i);
+        const double d = col[v * vxs] / n;
         const double r = d - (double)target[idx];
         if (soft) soft[idx] = (float)d;
-        resid[idx] = r;
+        if (GRAD) coef[v] = (T)(2.0 * r / (n * tau));
         r2 = r * r;
     }
-    const double tot = block_total(r2, col);
+    const double tot = block_total(r2, col);       // (barriers: coef is complete)
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
+    if (!GRAD) return;
+    const size_t W = (size_t)a.W;
+    for (int64_t c = x.xa + threadIdx.x; c < x.xb; c += kDThreads) {
+        const T cf = coef[(int32_t)(c / a.vx) - x.ia];
+        for (int32_t k = x.ka; k < x.kb; ++k) {
+            const size_t base = ((size_t)k * (size_t)a.H + (size_t)x.ya) * W + (size_t)c;
+            const T* p = field + base;
+            T* o = grad + base;
+            int32_t y = x.ya;
+            for (; y + kRowBatch <= x.yb; y += kRowBatch) {
+                T g[kRowBatch];
+#pragma unroll
+                for (int q = 0; q < kRowBatch; ++q) g[q] = p[(size_t)q * W];
+#pragma unroll
+                for (int q = 0; q < kRowBatch; ++q)
+                    __builtin_nontemporal_store(cf * sigm_prime((g[q] - C) * inv_tau),
+                                                o + (size_t)q * W);
+                p += kRowBatch * W;
+                o += kRowBatch * W;
+            }
+            for (; y < x.yb; ++y, p += W, o += W)
+                __builtin_nontemporal_store(cf * sigm_prime((*p - C) * inv_tau), o);
+        }
+    }
 }
 
 // one block: thread t sums partials t, t + 256, ... in four interleaved
@@ -213,40 +245,6 @@ __global__ __launch_bounds__(kDThreads) void k_loss_final(const double* part, ui
     for (int q = 0; b < nb; b += kDThreads, ++q) v[q] += part[b];
     const double tot = block_total((v[0] + v[1]) + (v[2] + v[3]), sm);
     if (threadIdx.x == 0) *loss = tot;
-}
-
-// dL/dg per pixel; every pixel of the field lies in exactly one block's box.
-// The gradient is written once and not read back here: streaming stores.
-template <typename T>
-__global__ __launch_bounds__(kDThreads) void k_density_grad(const T* field, DensityArgs a, T C,
-                                                            T inv_tau, double tau,
-                                                            const double* resid, T* grad) {
-    const Box x = block_box(a, blockIdx.x);
-    const size_t W = (size_t)a.W;
-    for (int64_t c = x.xa + threadIdx.x; c < x.xb; c += kDThreads) {
-        const int32_t i = (int32_t)(c / a.vx);
-        const size_t idx = ((size_t)x.l * (size_t)a.ny + (size_t)x.j) * (size_t)a.nx + (size_t)i;
-        const T coef = (T)(2.0 * resid[idx] / (box_samples(a, x, i) * tau));
-        for (int32_t k = x.ka; k < x.kb; ++k) {
-            const size_t base = ((size_t)k * (size_t)a.H + (size_t)x.ya) * W + (size_t)c;
-            const T* p = field + base;
-            T* o = grad + base;
-            int32_t y = x.ya;
-            for (; y + kRowBatch <= x.yb; y += kRowBatch) {
-                T v[kRowBatch];
-#pragma unroll
-                for (int q = 0; q < kRowBatch; ++q) v[q] = p[(size_t)q * W];
-#pragma unroll
-                for (int q = 0; q < kRowBatch; ++q)
-                    __builtin_nontemporal_store(coef * sigm_prime((v[q] - C) * inv_tau),
-                                                o + (size_t)q * W);
-                p += kRowBatch * W;
-                o += kRowBatch * W;
-            }
-            for (; y < x.yb; ++y, p += W, o += W)
-                __builtin_nontemporal_store(coef * sigm_prime((*p - C) * inv_tau), o);
-        }
-    }
 }
 
 // Per-pixel soft-occupancy loss: L = sum_p (s_p - t_p)^2, s = sigmoid((g - C)
@@ -310,15 +308,18 @@ template <typename T>
 lsl_status loss_t(const DensityArgs& a, const void* field, double C, double tau,
                   const float* target, float* soft, void* grad, double* loss, double* scratch,
                   hipStream_t st) {
-    double* resid = scratch;
-    double* part = scratch + density_voxels(a);
+    double* part = scratch;
     const T inv_tau = (T)(1.0 / tau);
-    k_soft_density<T><<<a.n_blocks, kDThreads, 0, st>>>((const T*)field, a, (T)C, inv_tau, target,
-                                                        soft, resid, part);
-    if (loss) k_loss_final<<<1, kDThreads, 0, st>>>(part, a.n_blocks, loss);
+    // the gradient's second pass reads what the first has just read: unused
+    // LDS holds the blocks in flight to four per compute unit
+    constexpr unsigned kPad = 36 * 1024;
     if (grad)
-        k_density_grad<T><<<a.n_blocks, kDThreads, 0, st>>>((const T*)field, a, (T)C, inv_tau,
-                                                            tau, resid, (T*)grad);
+        k_soft_density<T, true><<<a.n_blocks, kDThreads, kPad, st>>>(
+            (const T*)field, a, (T)C, inv_tau, tau, target, soft, (T*)grad, part);
+    else
+        k_soft_density<T, false><<<a.n_blocks, kDThreads, 0, st>>>(
+            (const T*)field, a, (T)C, inv_tau, tau, target, soft, nullptr, part);
+    if (loss) k_loss_final<<<1, kDThreads, 0, st>>>(part, a.n_blocks, loss);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }
@@ -356,7 +357,7 @@ size_t density_voxels(const DensityArgs& a) {
     return (size_t)a.nx * (size_t)a.ny * (size_t)a.nz;
 }
 
-size_t density_scratch_elems(const DensityArgs& a) { return density_voxels(a) + a.n_blocks; }
+size_t density_scratch_elems(const DensityArgs& a) { return a.n_blocks; }
 
 lsl_status launch_density(int dtype, const DensityArgs& a, const void* field, double C,
                           float* out, hipStream_t st) {

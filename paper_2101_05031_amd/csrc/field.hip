@@ -47,9 +47,9 @@
 namespace lsl {
 namespace {
 
-template <typename T, int SZ, bool STATS, int K, bool SR, bool PR>
+template <typename T, int SZ, bool STATS, int K, bool SR, int FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_field(FieldArgs a, uint32_t n_items) {
-    const int wv = threadIdx.x >> 6;
+    const int wv = wave_index();
     const uint32_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const uint32_t item = blk * 4u + (uint32_t)wv;
     if (item >= n_items) return;
@@ -62,12 +62,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     t /= (uint32_t)a.ntx;
     const int ty = (int)(t % (uint32_t)a.nty);
     t /= (uint32_t)a.nty;
-    // float32, the paper's kernel, shared reference planes: field_q32.hpp;
-    // otherwise (float64, the Gaussian, every plane its own reference)
-    // field_block.hpp
-    if constexpr (std::is_same<T, float>::value && K == LSL_KERNEL_QUARTIC && !PR) {
+    if constexpr (FORM != kFormBlock) {
         __shared__ q32::Lds<SZ> lds[4];
-        q32::field_block<SZ, STATS, SR>(a, a.s_lo + (int)t, tx, ty, sub, lds[wv]);
+        q32::field_block<SZ, STATS, SR, FORM == kFormAligned>(a, a.s_lo + (int)t, tx, ty, sub,
+                                                              lds[wv]);
     } else {
         __shared__ Stage<T> stage[4][kWave];
         __shared__ T pend[4][fieldk::pend_elems<T, SZ>()];
@@ -113,25 +111,28 @@ __global__ __launch_bounds__(256) void k_bits_blk(const T* field, int32_t nk, in
     if (lane < 8 && c * 8 + lane < nbx) out[kb * (uint64_t)nbx + (uint64_t)(c * 8 + lane)] = word;
 }
 
-template <typename T, int SZ, int K, bool SR, bool PR>
+template <typename T, int SZ, int K, bool SR, int FORM>
 lsl_status launch_tkp(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_t st) {
     const unsigned blocks = (n_items + 3u) / 4u;
     if (stats)
-        k_field<T, SZ, true, K, SR, PR><<<blocks, 256, 0, st>>>(a, n_items);
+        k_field<T, SZ, true, K, SR, FORM><<<blocks, 256, 0, st>>>(a, n_items);
     else
-        k_field<T, SZ, false, K, SR, PR><<<blocks, 256, 0, st>>>(a, n_items);
+        k_field<T, SZ, false, K, SR, FORM><<<blocks, 256, 0, st>>>(a, n_items);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }
 
-// Coarse planes (every plane its own reference) matter to the float32
-// kernel of the paper's kernel only.
 template <typename T, int SZ, int K, bool SR>
 lsl_status launch_tk(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_t st) {
     if constexpr (std::is_same<T, float>::value && K == LSL_KERNEL_QUARTIC) {
-        if (a.plane_ref) return launch_tkp<T, SZ, K, SR, true>(a, stats, n_items, st);
+        if constexpr (SZ >= 8) {
+            if (field_form(a, SZ) == kFormAligned)
+                return launch_tkp<T, SZ, K, SR, kFormAligned>(a, stats, n_items, st);
+        }
+        if (field_form(a, SZ) != kFormBlock)
+            return launch_tkp<T, SZ, K, SR, kFormGeneral>(a, stats, n_items, st);
     }
-    return launch_tkp<T, SZ, K, SR, false>(a, stats, n_items, st);
+    return launch_tkp<T, SZ, K, SR, kFormBlock>(a, stats, n_items, st);
 }
 
 template <typename T, int SZ>
@@ -145,11 +146,13 @@ lsl_status launch_t(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_
 
 template <typename T>
 lsl_status launch_dt(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_t st) {
-    if (a.slab <= 1) return launch_t<T, 1>(a, stats, n_items, st);
-    if (a.slab <= 2) return launch_t<T, 2>(a, stats, n_items, st);
-    if (a.slab <= 4) return launch_t<T, 4>(a, stats, n_items, st);
-    if (a.slab <= 8) return launch_t<T, 8>(a, stats, n_items, st);
-    return launch_t<T, 16>(a, stats, n_items, st);
+    switch (slab_planes(a.slab, a.nk)) {
+        case 1: return launch_t<T, 1>(a, stats, n_items, st);
+        case 2: return launch_t<T, 2>(a, stats, n_items, st);
+        case 4: return launch_t<T, 4>(a, stats, n_items, st);
+        case 8: return launch_t<T, 8>(a, stats, n_items, st);
+        default: return launch_t<T, 16>(a, stats, n_items, st);
+    }
 }
 
 }  // namespace

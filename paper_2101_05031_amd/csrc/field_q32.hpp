@@ -109,67 +109,145 @@ __device__ __forceinline__ double uniform(double v) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// keeps a value in a vector register from here on
+__device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)); }
+
 __device__ __forceinline__ void comp_add(float g, float& s, float& c) {
     const float sn = s + g;
     c += g - (sn - s);
     s = sn;
 }
 
-// The terms of one candidate strut (staging lane e, planes `mask`, uniform;
-// E, nD and the planes' G_k its staged values) at the pixel d = (dX, dY) of each plane it
-// reaches, added to the open runs of the planes of the slab that starts at
-// plane kb (reference group gb).
-template <int SZ, bool STATS>
-__device__ __forceinline__ void add_candidate(const Lds<SZ>& L, uint32_t e,
-                                              uint32_t mask, float4 E, float nD, int kb, int gb,
-                                              const float (&Gk)[SZ], float dX, float dY,
-                                              float nd2, bool pix, float (&acc_s)[SZ],
-                                              float (&acc_c)[SZ], float (&run)[SZ],
-                                              int (&open)[SZ], unsigned long long& n_cand,
-                                              unsigned long long& n_useful) {
-    const float du = __builtin_fmaf(dX, E.x, dY * E.y);        // d.u^
-    const float P1 = E.z * du;
-    const float ndd = nd2 * E.w;                                // -|d^|^2
-    float Eg = 0.0f, ar = 0.0f, br = 0.0f;
-    int gcur = -1;
+// The lane's sums: per plane the compensated sum (acc_s + acc_c) and the
+// open run with its number of terms (uniform).
+template <int SZ>
+struct Sums {
+    float acc_s[SZ], acc_c[SZ], run[SZ];
+    int open[SZ];
+    __device__ __forceinline__ void clear() {
+        for_planes<0, SZ>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            acc_s[k] = acc_c[k] = run[k] = 0.0f;
+            open[k] = 0;
+        });
+    }
+};
+
+// Adds the terms of n candidates at the pixel d = (dX, dY), nd2 = -|d|^2, of
+// each plane they reach, to the sums of the SZ planes from kb on.  Lane r of
+// cv holds candidate r: its staged lane | plane mask << 8.
+//
+// The loop is bound by the vector ALU's issue: a full-rate instruction takes
+// a SIMD about 2.6 cycles, one with a scalar register among its operands 4.4,
+// a clamp 4.4, an integer shift-add 4.7, the square root 8.1.  So a
+// candidate's LDS addresses are formed in scalar registers (its code is read
+// from lane r of cv), and with planes aligned to the reference groups (AL: kb
+// a multiple of 8) kappa is a constant of the unrolled plane, plane 0 of a
+// group needs no shift, and a group's values are formed once per candidate;
+// otherwise kappa waits in a vector register per plane.  AL_MEASURED
+template <int SZ, bool STATS, bool AL>
+__device__ __forceinline__ void add_candidates(const Lds<SZ>& L, uint32_t cv, int n, int kb,
+                                               float dX, float dY, float nd2, bool pix,
+                                               const float (&kapv)[SZ], Sums<SZ>& S,
+                                               unsigned long long& n_cand,
+                                               unsigned long long& n_useful) {
+    const int gb = kb >> 3;
+#pragma unroll 1
+    for (int j = 0; j < n; ++j) {
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cv, j);
+        const uint32_t e = c & 63u, mask = c >> 8;
+        // all of the candidate's values in one round trip (the empty asm keeps
+        // the reads from sinking to their uses, each behind a wait of its own)
+        float4 E = L.e[e], R0 = L.gr[0][e];
+        float nD = L.dl[e];
+        float Gk[SZ];
+        for_planes<0, SZ>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            Gk[k] = L.pg[k][e];
+        });
+        pin(E.x);
+        pin(E.y);
+        pin(E.z);
+        pin(E.w);
+        pin(R0.x);
+        pin(R0.y);
+        pin(R0.z);
+        pin(R0.w);
+        pin(nD);
+        for_planes<0, SZ>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            pin(Gk[k]);
+        });
+        const float du = __builtin_fmaf(dX, E.x, dY * E.y);        // d.u^
+        const float P1 = E.z * du;
+        const float ndd = nd2 * E.w;                                // -|d^|^2
+        float Eg = 0.0f, ar = 0.0f, br = 0.0f;
+        int gcur = -1;
+        for_planes<0, SZ>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            auto group = [&](float4 Rg) {
+                ar = Rg.x - du;
+                br = Rg.y - du;
+                Eg = __builtin_fmaf(du, du, __builtin_fmaf(Rg.z, dX, __builtin_fmaf(Rg.w, dY, ndd)));
+            };
+            if constexpr (AL && (k & 7) == 0) group(k == 0 ? R0 : L.gr[k >> 3][e]);
+            if (!((mask >> k) & 1u)) return;
+            if constexpr (!AL) {
+                const int g = ((kb + k) >> 3) - gb;
+                if (g != gcur) {
+                    group(g == 0 ? R0 : L.gr[g][e]);
+                    gcur = g;
+                }
+            }
+            float al, be, Hp;
+            if constexpr (AL && (k & 7) == 0) {
+                al = ar;
+                be = br;
+                Hp = Gk[k] + Eg;
+            } else {
+                const float kap = AL ? (float)(k & 7) : kapv[k];
+                al = __builtin_fmaf(kap, nD, ar);
+                be = __builtin_fmaf(kap, nD, br);
+                Hp = __builtin_fmaf(kap, P1, Gk[k] + Eg);
+            }
+            const float H = __builtin_amdgcn_fmed3f(Hp, 0.0f, 1.0f);
+            const float h = __builtin_amdgcn_sqrtf(H);
+            const float ca = __builtin_amdgcn_fmed3f(al, -h, h);
+            const float cb = __builtin_amdgcn_fmed3f(be, -h, h);
+            const float s = ca + cb, D = cb - ca;
+            const float s2 = s * s, D2 = D * D;
+            const float A = __builtin_fmaf(D2, -1.0f / 12.0f, __builtin_fmaf(s2, -0.25f, H));
+            const float V = __builtin_fmaf(s2, 1.0f / 12.0f, D2 * (1.0f / 180.0f));
+            const float Q = __builtin_fmaf(A, A, D2 * V);
+            if (STATS) {
+                n_cand += pix ? 1ull : 0ull;
+                n_useful += (pix && D * Q > 0.0f) ? 1ull : 0ull;
+            }
+            S.run[k] = __builtin_fmaf(D, Q, S.run[k]);
+            if (++S.open[k] == kRun) {
+                comp_add(S.run[k], S.acc_s[k], S.acc_c[k]);
+                S.run[k] = 0.0f;
+                S.open[k] = 0;
+            }
+        });
+    }
+}
+
+// The vector registers of kappa for planes kb .. kb + SZ - 1 (not AL).
+template <int SZ>
+__device__ __forceinline__ void kappa_regs(int kb, float (&kapv)[SZ]) {
     for_planes<0, SZ>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        if (!((mask >> k) & 1u)) return;
-        const int g = ((kb + k) >> 3) - gb;
-        if (g != gcur) {
-            const float4 Rg = L.gr[g][e];
-            ar = Rg.x - du;
-            br = Rg.y - du;
-            Eg = __builtin_fmaf(du, du, __builtin_fmaf(Rg.z, dX, __builtin_fmaf(Rg.w, dY, ndd)));
-            gcur = g;
-        }
-        const float kap = kappa((kb + k) & 7);
-        const float al = __builtin_fmaf(kap, nD, ar);
-        const float be = __builtin_fmaf(kap, nD, br);
-        const float H = __builtin_amdgcn_fmed3f(__builtin_fmaf(kap, P1, Gk[k] + Eg), 0.0f, 1.0f);
-        const float h = __builtin_amdgcn_sqrtf(H);
-        const float ca = __builtin_amdgcn_fmed3f(al, -h, h);
-        const float cb = __builtin_amdgcn_fmed3f(be, -h, h);
-        const float s = ca + cb, D = cb - ca;
-        const float s2 = s * s, D2 = D * D;
-        const float A = __builtin_fmaf(D2, -1.0f / 12.0f, __builtin_fmaf(s2, -0.25f, H));
-        const float V = __builtin_fmaf(s2, 1.0f / 12.0f, D2 * (1.0f / 180.0f));
-        const float Q = __builtin_fmaf(A, A, D2 * V);
-        if (STATS) {
-            n_cand += pix ? 1ull : 0ull;
-            n_useful += (pix && D * Q > 0.0f) ? 1ull : 0ull;
-        }
-        run[k] = __builtin_fmaf(D, Q, run[k]);
-        if (++open[k] == kRun) {
-            comp_add(run[k], acc_s[k], acc_c[k]);
-            run[k] = 0.0f;
-            open[k] = 0;
-        }
-    });}
+        kapv[k] = kappa((kb + k) & 7);
+        pin(kapv[k]);
+    });
+}
 
 // One wave: the 8x8 block `sub` of tile (tx, ty) over the planes of `slab`
-// in [k0, k0+nk).
-template <int SZ, bool STATS, bool SR>
+// in [k0, k0+nk).  AL: the slab is a whole number of reference groups (8 or
+// 16 planes, SZ of them); planes are then counted from its first one, whether
+// in the range or not.
+template <int SZ, bool STATS, bool SR, bool AL>
 __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx, int ty, int sub,
                                             Lds<SZ>& L) {
     const int lane = lane_id();
@@ -178,10 +256,13 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
     const int i0 = tx * a.tile + (sub % nsub) * kBlockPix;
     const int j0 = ty * a.tile + (sub / nsub) * kBlockPix;
     if (i0 >= a.W || j0 >= a.H) return;
-    int kb = slab * a.slab, ke = kb + a.slab;
-    if (kb < a.k0) kb = a.k0;
+    int kb = slab * a.slab, ke = kb + a.slab, kfirst = 0;
+    if (kb < a.k0) {
+        if (AL) kfirst = a.k0 - kb;
+        else kb = a.k0;
+    }
     if (ke > a.k0 + a.nk) ke = a.k0 + a.nk;
-    const int nvalid = ke - kb;
+    const int nvalid = ke - kb;                 // planes kb + kfirst .. kb + nvalid - 1
     const int gb = kb >> 3;                     // first reference group
 
     const uint32_t bucket = ((uint32_t)(slab - a.group_s0) * (uint32_t)a.nty + (uint32_t)ty) *
@@ -205,13 +286,10 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
     const int ie = i0 + 7 < a.W - 1 ? i0 + 7 : a.W - 1;
     const int je = j0 + 7 < a.H - 1 ? j0 + 7 : a.H - 1;
 
-    float acc_s[SZ], acc_c[SZ], run[SZ];
-    int open[SZ];                               // terms in each plane's open run (uniform)
-    for_planes<0, SZ>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        acc_s[k] = acc_c[k] = run[k] = 0.0f;
-        open[k] = 0;
-    });
+    Sums<SZ> S;
+    S.clear();
+    float kapv[SZ];
+    if constexpr (!AL) kappa_regs<SZ>(kb, kapv);
     unsigned long long n_cand = 0, n_useful = 0;
 
     const StrutRec<float>* recs = (const StrutRec<float>*)a.rec;
@@ -267,7 +345,7 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
         // one plane at a time: the float64 temporaries of several planes in
         // flight would cost registers the evaluation needs
 #pragma unroll 1
-        for (int k = 0; k < nvalid; ++k) {
+        for (int k = kfirst; k < nvalid; ++k) {
             const int ka = kb + k;
             const int g = ka >> 3;
             if (g != grp) {
@@ -320,34 +398,14 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
         const int n = __popcll(cm);
 
         // ------------------------------------------------------- evaluation
-        // The next candidate's values are read while this one is evaluated.
-        uint32_t c = L.cand[0];
-        float4 E = L.e[c & 63u];
-        float nD = L.dl[c & 63u];
-#pragma unroll 1
-        for (int j = 0; j < n; ++j) {
-            const uint32_t e = c & 63u;
-            const uint32_t mask = __builtin_amdgcn_readfirstlane(c >> 8);
-            float Gk[SZ];
-            for_planes<0, SZ>([&](auto kc) {
-                constexpr int k = decltype(kc)::value;
-                Gk[k] = L.pg[k][e];
-            });
-            const uint32_t cn = L.cand[j + 1 < n ? j + 1 : j];
-            const float4 En = L.e[cn & 63u];
-            const float nDn = L.dl[cn & 63u];
-            add_candidate<SZ, STATS>(L, e, mask, E, nD, kb, gb, Gk, dX, dY, nd2, pix,
-                                                acc_s, acc_c, run, open, n_cand, n_useful);
-            c = cn;
-            E = En;
-            nD = nDn;
-        }
+        const uint32_t cv = L.cand[lane];
+        add_candidates<SZ, STATS, AL>(L, cv, n, kb, dX, dY, nd2, pix, kapv, S, n_cand, n_useful);
         __builtin_amdgcn_wave_barrier();
     }
 
     for_planes<0, SZ>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        if (open[k] != 0) comp_add(run[k], acc_s[k], acc_c[k]);
+        if (S.open[k] != 0) comp_add(S.run[k], S.acc_s[k], S.acc_c[k]);
     });
 
     if (STATS) {
@@ -356,7 +414,7 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
             n_cand += __shfl_xor(n_cand, d, kWave);
             n_useful += __shfl_xor(n_useful, d, kWave);
         }
-        const unsigned long long npx = (unsigned long long)__popcll(ballot64(pix)) * nvalid;
+        const unsigned long long npx = (unsigned long long)__popcll(ballot64(pix)) * (nvalid - kfirst);
         if (lane == 0) {
             atomicAdd(&a.stats[0], n_cand);
             atomicAdd(&a.stats[1], n_useful);
@@ -368,9 +426,9 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
         float* out = (float*)a.field;
         for_planes<0, SZ>([&](auto kc) {
             constexpr int k = decltype(kc)::value;
-            if (k < nvalid)
+            if (k >= kfirst && k < nvalid)
                 out[((size_t)(kb + k - a.k0) * (size_t)a.H + (size_t)pj) * (size_t)a.W + (size_t)pi] =
-                    __builtin_ldexpf(acc_s[k] + acc_c[k], 5 * a.wexp);
+                    __builtin_ldexpf(S.acc_s[k] + S.acc_c[k], 5 * a.wexp);
         });
     }
     if (a.bits_blk) {
@@ -378,9 +436,9 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
         const float C = (float)a.C;
         for_planes<0, SZ>([&](auto kc) {
             constexpr int k = decltype(kc)::value;
-            if (k < nvalid) {
+            if (k >= kfirst && k < nvalid) {
                 const uint64_t m =
-                    ballot64(pix && __builtin_ldexpf(acc_s[k] + acc_c[k], 5 * a.wexp) >= C);
+                    ballot64(pix && __builtin_ldexpf(S.acc_s[k] + S.acc_c[k], 5 * a.wexp) >= C);
                 if (lane == 0)
                     a.bits_blk[((size_t)(kb + k - a.k0) * nby + (size_t)(j0 >> 3)) * nbx +
                                (size_t)(i0 >> 3)] = m;

@@ -143,6 +143,25 @@ struct FieldArgs {
     double C;
     unsigned long long* stats;        // [3] (stats kernels only)
 };
+// The planes per slab that the field kernels are built for: the power of two
+// that holds the planes a call evaluates in any slab.  A call for fewer
+// planes than a slab holds takes the smaller kernel (the field does not
+// depend on the choice): fewer registers and less LDS per wave, and no passes
+// over planes outside the range.  One plane of 2048^2 of 463k struts:
+// SZ_MEASURED.
+inline int slab_planes(int32_t slab, int32_t nk) {
+    const int32_t m = slab < nk ? slab : nk;
+    return m <= 1 ? 1 : m <= 2 ? 2 : m <= 4 ? 4 : m <= 8 ? 8 : 16;
+}
+// The form of the float32 kernel of the paper's kernel: field_q32.hpp with
+// planes that share reference planes (aligned: slabs of whole reference groups,
+// all SZ planes of which the kernel holds), or field_block.hpp, which also
+// serves float64 and the Gaussian.
+enum { kFormBlock = 0, kFormGeneral = 1, kFormAligned = 2 };
+inline int field_form(const FieldArgs& a, int SZ) {
+    if (a.plane_ref) return kFormBlock;
+    return a.slab == SZ && a.slab % 8 == 0 ? kFormAligned : kFormGeneral;
+}
 lsl_status launch_field(int dtype, const FieldArgs& a, bool stats, hipStream_t st);
 // Block-major binary image (see FieldArgs::bits_blk) of a field.
 lsl_status launch_bits_blk(int dtype, const void* field, int32_t nk, int32_t W, int32_t H,
@@ -238,8 +257,7 @@ lsl_status launch_queue_build(const FieldArgs& f, uint32_t* keys, uint32_t* vals
                               uint32_t* keys_alt, uint32_t* vals_alt, uint32_t n_items,
                               uint32_t* tmp, const uint32_t** queue_out, hipStream_t st);
 // The caller zeroes a.counter before the launch.
-lsl_status launch_persistent(int dtype, const BatchArgs& a, int n_blocks, hipStream_t st);
-int persistent_blocks(int dtype, int slab);
+lsl_status launch_persistent(int dtype, const BatchArgs& a, hipStream_t st);
 
 // ---------------------------------------------------------------- support.hip
 // Self-support metrics (Sec. 5.2, Eqs. 11-14) and dGamma/dv.
@@ -273,7 +291,7 @@ struct DensityArgs {
 lsl_status density_plan(int32_t nk, int32_t W, int32_t H, int32_t vx, int32_t vy, int32_t vz,
                         DensityArgs* a);
 size_t density_voxels(const DensityArgs& a);
-// doubles: residuals [voxels] + per-block partial losses [n_blocks]
+// doubles: per-block partial losses [n_blocks]
 size_t density_scratch_elems(const DensityArgs& a);
 lsl_status launch_density(int dtype, const DensityArgs& a, const void* field, double C,
                           float* out, hipStream_t st);

@@ -43,12 +43,19 @@ __device__ __forceinline__ uint64_t double_key(double z) {
 // Plan histograms live in LDS per block when the slab count allows it.
 constexpr int kLdsSlabs = 2048;
 
+// Every block adds its histograms to the plan's with one atomic per counter
+// and slab, and those meet on a few addresses (about 10 ns each): one block
+// of 1024 threads per compute unit, and the extremes reduced over the block
+// first, keep them few.  1M struts in 12 slabs: PREP_MEASURED.
+constexpr int kPrepThreads = 1024;
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
+__global__ __launch_bounds__(kPrepThreads) void k_prep(PrepArgs a) {
     __shared__ uint32_t h_lo[kLdsSlabs], h_hi[kLdsSlabs];
     __shared__ unsigned long long h_pairs[kLdsSlabs + 1];
     __shared__ uint32_t h_rows[kLdsSlabs + 1];   // modulo 2^32: a slab's rows are < 2^32
-    __shared__ uint32_t h_n;
+    __shared__ uint32_t h_n, h_inv, h_wr;
+    if (threadIdx.x == 0) h_inv = h_wr = 0u;
     const bool lds = a.n_slabs <= kLdsSlabs;
     if (lds) {
         for (int i = threadIdx.x; i < a.n_slabs; i += blockDim.x) {
@@ -185,26 +192,25 @@ __global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
             }
         }
     }
-    // the smallest support of a binned strut
-    if (a.support && a.min_support) {
-        uint32_t inv = inv_acc;
-        for (int d = 32; d >= 1; d >>= 1) {
-            const uint32_t o = (uint32_t)__shfl_xor((int)inv, d, kWave);
-            inv = inv > o ? inv : o;
-        }
-        if ((threadIdx.x & (kWave - 1)) == 0 && inv != 0u) atomicMax(a.min_support, inv);
+    // the smallest support of a binned strut, and the largest r R of one (the
+    // float32 field kernel's scale)
+    __syncthreads();
+    for (int d = 32; d >= 1; d >>= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)inv_acc, d, kWave);
+        const uint32_t v = (uint32_t)__shfl_xor((int)wr_acc, d, kWave);
+        inv_acc = inv_acc > o ? inv_acc : o;
+        wr_acc = wr_acc > v ? wr_acc : v;
     }
-    // the largest r R of a binned strut (the float32 field kernel's scale)
-    if (a.max_wr) {
-        uint32_t v = wr_acc;
-        for (int d = 32; d >= 1; d >>= 1) {
-            const uint32_t o = (uint32_t)__shfl_xor((int)v, d, kWave);
-            v = v > o ? v : o;
-        }
-        if ((threadIdx.x & (kWave - 1)) == 0 && v != 0u) atomicMax(a.max_wr, v);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicMax(&h_inv, inv_acc);
+        atomicMax(&h_wr, wr_acc);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (a.support && a.min_support && h_inv) atomicMax(a.min_support, h_inv);
+        if (a.max_wr && h_wr) atomicMax(a.max_wr, h_wr);
     }
     if (lds) {
-        __syncthreads();
         for (int i = threadIdx.x; i < a.n_slabs; i += blockDim.x) {
             if (h_lo[i]) atomicAdd(&a.cnt_lo[i], h_lo[i]);
             if (h_hi[i]) atomicAdd(&a.cnt_hi[i], h_hi[i]);
@@ -265,15 +271,15 @@ lsl_status launch_prep(int dtype, const PrepArgs& a, hipStream_t st) {
     int dev = 0, cus = 0;
     LSL_HIP(hipGetDevice(&dev));
     LSL_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // four blocks per compute unit (the histograms' LDS allows that many),
-    // each over a contiguous range of at least 256 edges
-    const int64_t by_edges = (a.n_edges + 255) / 256;
-    const int64_t cap = 4 * (int64_t)(cus > 0 ? cus : 1);
+    // at most one block per compute unit, each over a contiguous range of at
+    // least 1024 edges
+    const int64_t by_edges = (a.n_edges + kPrepThreads - 1) / kPrepThreads;
+    const int64_t cap = (int64_t)(cus > 0 ? cus : 1);
     const unsigned g = (unsigned)(by_edges < cap ? by_edges : cap);
     if (dtype == LSL_F32)
-        k_prep<float><<<g, 256, 0, st>>>(a);
+        k_prep<float><<<g, kPrepThreads, 0, st>>>(a);
     else
-        k_prep<double><<<g, 256, 0, st>>>(a);
+        k_prep<double><<<g, kPrepThreads, 0, st>>>(a);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }

@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void k_probe_f64(double* out, int iters, doubl
 // The float32 field kernel's evaluation alone: every wave one 8x8 block, 64
 // struts staged in LDS as the kernel stages them (a slab of 8 planes sharing
 // one reference plane), each a candidate at every plane, the terms formed and
-// summed by the kernel's own code (q32::add_candidate).  The staged values
+// summed by the kernel's own code (q32::add_candidates).  The staged values
 // put every pixel inside every strut's support.
 __global__ __launch_bounds__(256) void k_probe_term(float* out, int iters) {
     constexpr int SZ = 8;
@@ -66,41 +66,17 @@ __global__ __launch_bounds__(256) void k_probe_term(float* out, int iters) {
     __builtin_amdgcn_wave_barrier();
     const float dX = 0.05f * ((float)(lane & 7) - 3.5f), dY = 0.05f * ((float)(lane >> 3) - 3.5f);
     const float nd2 = -(dX * dX + dY * dY);
-    float acc_s[SZ], acc_c[SZ], run[SZ];
-    int open[SZ];
-    q32::for_planes<0, SZ>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        acc_s[k] = acc_c[k] = run[k] = 0.0f;
-        open[k] = 0;
-    });
+    q32::Sums<SZ> S;
+    S.clear();
+    const float kapv[SZ] = {};                 // (aligned planes need none)
     unsigned long long n_cand = 0, n_useful = 0;
-    for (int i = 0; i < iters; ++i) {
-        uint32_t c = L.cand[0];
-        float4 E = L.e[c & 63u];
-        float nD = L.dl[c & 63u];
-#pragma unroll 1
-        for (int j = 0; j < kWave; ++j) {
-            const uint32_t e = c & 63u;
-            const uint32_t mask = __builtin_amdgcn_readfirstlane(c >> 8);
-            float Gk[SZ];
-            q32::for_planes<0, SZ>([&](auto kc) {
-                constexpr int k = decltype(kc)::value;
-                Gk[k] = L.pg[k][e];
-            });
-            const uint32_t cn = L.cand[j + 1 < kWave ? j + 1 : j];
-            const float4 En = L.e[cn & 63u];
-            const float nDn = L.dl[cn & 63u];
-            q32::add_candidate<SZ, false>(L, e, mask, E, nD, 0, 0, Gk, dX, dY, nd2, true,
-                                                 acc_s, acc_c, run, open, n_cand, n_useful);
-            c = cn;
-            E = En;
-            nD = nDn;
-        }
-    }
+    for (int i = 0; i < iters; ++i)
+        q32::add_candidates<SZ, false, true>(L, L.cand[lane], kWave, 0, dX, dY, nd2, true, kapv, S,
+                                             n_cand, n_useful);
     float t = 0.0f;
     q32::for_planes<0, SZ>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        t += acc_s[k] + acc_c[k] + run[k];
+        t += S.acc_s[k] + S.acc_c[k] + S.run[k];
     });
     out[blockIdx.x * 256 + threadIdx.x] = t;
 }

@@ -24,11 +24,12 @@ def lattice(n, dtype, seed):
     return nodes, np.ascontiguousarray(edges), np.full(n, 0.5, dtype)
 
 
-# one block (up to 8192 items), a tile of 2048, the histogram summed by every
-# block (up to 64 blocks, 131072 items) or scanned row by row
+# one block (up to 8192 items, in rounds of 1024), a tile of 2048, the
+# histogram summed by every block (up to 16 blocks, 32768 items) or scanned
+# row by row
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
-@pytest.mark.parametrize("n", [1, 2, 63, 65, 511, 513, 8191, 8192, 8193, 10241, 131071, 131072,
-                               131073, 200003])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 511, 513, 1023, 1025, 8191, 8192, 8193, 10241,
+                               32767, 32768, 32769, 200003])
 def test_edge_list_is_the_stable_sort(n, dtype):
     nodes, edges, w = lattice(n, dtype, n)
     grid = synth.Grid(-25.0, -25.0, 1.0, 1.0, 50, 50, -20.0, 0.5, 80)
