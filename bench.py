@@ -8,7 +8,7 @@ tetrahedral configuration at one million struts.  Seeded synthetic input.
 
 A step is one pass of the whole path over the lattice, inputs already in HBM:
   lattice_bin (strut prep, z-ordered edge list, slab/tile buckets)
-  slice_batch (persistent field kernel, binary image, marching squares)
+  slice_batch (field kernel in work-queue order, binary image, marching squares)
 and, for the fwd+bwd step, a soft-occupancy loss on the field (torch
 elementwise) and slice_field_backward over all planes.
 
@@ -452,7 +452,7 @@ def main():
         },
         "roofline": {
             "bound": "alu",
-            "kernel": "k_persistent (field)",
+            "kernel": "k_field (work-queue order)",
             "achieved": None if achieved is None else achieved / 1e12,
             "peak": peak / 1e12,
             "unit": "TFLOP/s",

@@ -123,7 +123,7 @@ typedef struct lsl_bins_info {
     int32_t dtype, tile, slab;
     int32_t tiles_x, tiles_y, n_slabs, n_groups;
     int32_t current_group;  /* group whose bucket lists are resident, or -1      */
-    double last_field_ms;   /* device time of the persistent field launches of
+    double last_field_ms;   /* device time of the field launches of
                                the last slice_batch call (HIP events around the
                                kernel on its stream); -1 if unavailable          */
     double last_group_bin_ms;   /* the same call's other stages, summed over its */
@@ -326,8 +326,8 @@ lsl_status slice_density(const lattice_bins* bins, int32_t nk, const void* field
  * ready for slice_field_backward.  target: [nz][ny][nx] float32 on the
  * device.  soft_density ([nz][ny][nx] float32), grad_field and loss are each
  * optional (NULL: not written).  Sums run in a fixed order (bitwise
- * repeatable).  Stream-ordered; keeps a scratch buffer of one float64 per
- * voxel on the bins handle (it grows, synchronising `stream`, when a call
+ * repeatable).  Stream-ordered; keeps a scratch buffer of at most one float64
+ * per voxel on the bins handle (it grows, synchronising `stream`, when a call
  * needs more).  LSL_EINVAL on extents < 1 or tau <= 0.
  * ------------------------------------------------------------------------- */
 lsl_status slice_density_loss(const lattice_bins* bins, int32_t nk, const void* field,
@@ -393,8 +393,8 @@ lsl_status slice_field_backward(lattice_bins* bins, int32_t k0, int32_t nk,
 
 /* ---------------------------------------------------------------------------
  * slice_batch -- planes k0 .. k0+nk-1 end to end (field, binary image,
- * contours) with one persistent field launch per slab group: work items
- * (slab, tile) are taken from a device queue in descending cost order, so
+ * contours) with one field launch per slab group: work items (slab, tile)
+ * are taken in the descending cost order of a device queue, so
  * planes with very different strut counts share the GPU evenly (Sec. 6.4:
  * slicing time follows the number of struts meeting a plane).  Each group's
  * launches run as three HIP graphs through the process's graph cache (see

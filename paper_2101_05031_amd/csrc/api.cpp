@@ -341,7 +341,7 @@ struct lattice_bins {
     size_t pscratch_elems = 0;
     double* dscratch = nullptr;       // slice_density_loss: residuals, block partials
     size_t dscratch_elems = 0;
-    uint32_t* queue_buf = nullptr;     // persistent path: keys/vals/alternates + counter
+    uint32_t* queue_buf = nullptr;     // batched path: keys/vals/alternates + running total
     size_t queue_cap = 0;
     std::vector<std::pair<void*, size_t>> allocs;
     int64_t dev_bytes = 0, peak_bytes = 0;
@@ -1172,7 +1172,7 @@ lsl_status slice_field(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
         a.group_s0 = b->groups[g].sa;
         a.s_lo = s_lo;
         a.s_hi = s_hi;
-        return launch_field(b->dtype, a, false, st);
+        return launch_field(b->dtype, a, false, nullptr, st);
     }));
     if (bits) LSL_TRY(launch_bits_rows((const uint64_t*)b->cbits, nk, b->grid.W, b->grid.H, bits, st));
     return LSL_OK;
@@ -1194,7 +1194,7 @@ lsl_status slice_field_stats(lattice_bins* b, int32_t k0, int32_t nk, int64_t* c
             a.s_lo = s_lo;
             a.s_hi = s_hi;
             a.stats = b->stats;
-            return launch_field(b->dtype, a, true, st);
+            return launch_field(b->dtype, a, true, nullptr, st);
         }));
     }
     unsigned long long h[4] = {0, 0, 0, 0};
@@ -1423,8 +1423,8 @@ struct GraphShape {
 };
 
 // Enqueues one phase of a group's part of slice_batch on `st`:
-//   0: work queue (descending cost) and counter reset
-//   1: persistent field kernel
+//   0: work queue (descending cost)
+//   1: field kernel
 //   2: binary image and contours (positions continue from the device-side
 //      running total of earlier groups)
 lsl_status batch_group_work(lattice_bins* b, int g, int32_t k0, int32_t nk, int s_lo, int s_hi,
@@ -1453,24 +1453,16 @@ lsl_status batch_group_work(lattice_bins* b, int g, int32_t k0, int32_t nk, int 
     uint32_t* qv = qk + b->queue_cap;
     uint32_t* qk2 = qv + b->queue_cap;
     uint32_t* qv2 = qk2 + b->queue_cap;
-    uint32_t* counter = qv2 + b->queue_cap;
-    uint32_t* qtmp = counter + 64;
-    unsigned long long* base = (unsigned long long*)(counter + 32);
+    unsigned long long* base = (unsigned long long*)(qv2 + b->queue_cap);
+    uint32_t* qtmp = qv2 + b->queue_cap + 64;
     if (phase == 0) {
         const uint32_t* queue = nullptr;
         LSL_TRY(launch_queue_build(a, qk, qv, qk2, qv2, n_items, qtmp, &queue, st));
-        LSL_TRY(fill_u32(counter, 0u, 1, st));
         b->queue_in_alt = queue != qv;
         return LSL_OK;
     }
-    if (phase == 1) {
-        BatchArgs ba{};
-        ba.f = a;
-        ba.queue = b->queue_in_alt ? qv2 : qv;
-        ba.n_items = n_items;
-        ba.counter = counter;
-        return launch_persistent(b->dtype, ba, st);
-    }
+    if (phase == 1)
+        return launch_field(b->dtype, a, false, b->queue_in_alt ? qv2 : qv, st);
     LSL_TRY(launch_contours_count(img, nkg, b->grid.W, b->grid.H, offsets + (kg0 - k0), nullptr,
                                   b->ctmp, base, st));
     LSL_TRY(launch_contours_emit(img, nkg, b->grid.W, b->grid.H, b->ctmp, base, segs, capacity,
@@ -1613,8 +1605,7 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
     LSL_TRY(b->grow(&b->ctmp, &b->ctmp_elems,
                     contour_tmp_elems((int32_t)max_planes, b->grid.W, b->grid.H), st));
     LSL_TRY(ensure_cbits(b, (int32_t)max_planes, st));
-    uint32_t* counter = b->queue_buf + 4 * b->queue_cap;
-    unsigned long long* base = (unsigned long long*)(counter + 32);
+    unsigned long long* base = (unsigned long long*)(b->queue_buf + 4 * b->queue_cap);
     LSL_TRY(fill_bytes0(base, 8, st));
     if (b->n_binned == 0 || b->groups.empty()) {
         // nothing binned: empty field, empty images, no segments

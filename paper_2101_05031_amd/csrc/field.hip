@@ -5,9 +5,8 @@
 // serves float64, the compact Gaussian and float32 lattices whose planes are
 // coarse against the smallest support (every plane staged from float64).
 //
-// One wave owns an 8x8 pixel block of one tile and one slab of planes; the
-// four waves of a workgroup take the four 8x8 blocks of a 16x16 tile (or
-// four of the blocks of a larger tile).  The wave walks its tile's bucket
+// One wave owns an 8x8 pixel block of one tile and one slab of planes.  The
+// wave walks its tile's bucket
 // list (edge-list order) 64 struts at a time.  Per strut and plane it stages,
 // in float64, the foot F of the block centre c on the strut's line:
 //
@@ -47,31 +46,55 @@
 namespace lsl {
 namespace {
 
+// Waves per SIMD the kernels are built for: the registers of one or two
+// planes fit eight (64 each), of four planes six; eight and more planes are
+// fastest with five (96 registers; four and six measured 9% and 3% slower).
+constexpr int field_waves(int SZ) { return SZ <= 2 ? 8 : SZ <= 4 ? 6 : 5; }
+
+// One wave per workgroup takes one 8x8 block of one (slab, tile) item.  The
+// items come in the order of `queue` (descending cost, slice_batch), the
+// hardware handing workgroups out as others end, or, without one, in order;
+// either way the blocks of an item follow each other on one XCD, whose L2
+// then holds the item's records (workgroups go to the 8 XCDs in turn).
+//
+// Workgroups of one wave: a workgroup's place is taken again only when all
+// its waves have ended, so four unequal blocks leave a compute unit partly
+// idle; and a grid of persistent workgroups that pull items from a counter
+// waits at each item for its slowest wave.  96 planes of 2048^2 of 1M struts:
+// persistent workgroups of four waves 8.0 ms, this 7.7 ms;
+// 812 float64 struts, 50 planes of 256^2: 54 and 36 us.
 template <typename T, int SZ, bool STATS, int K, bool SR, int FORM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_field(FieldArgs a, uint32_t n_items) {
-    const int wv = wave_index();
-    const uint32_t blk = xcd_remap(blockIdx.x, gridDim.x);
-    const uint32_t item = blk * 4u + (uint32_t)wv;
-    if (item >= n_items) return;
-    // item -> (slab, tile, 8x8 block): blocks of a tile are consecutive
-    const int nsub = a.tile / kBlockPix;
-    uint32_t t = item;
-    const int sub = (int)(t % (uint32_t)(nsub * nsub));
-    t /= (uint32_t)(nsub * nsub);
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(field_waves(SZ)))) void
+k_field(FieldArgs a, const uint32_t* queue, uint32_t item0, uint32_t n_items) {
+    const int nsub = a.tile / kBlockPix, nsub2 = nsub * nsub;
+    const uint32_t xcd = blockIdx.x % 8u, u = blockIdx.x / 8u;
+    const uint32_t seq = u / (uint32_t)nsub2;
+    const int sub = (int)(u % (uint32_t)nsub2);
+    uint32_t t;
+    if (queue) {
+        const uint32_t i = item0 + seq * 8u + xcd;
+        if (i >= n_items) return;
+        t = queue[i];
+    } else {
+        // each XCD walks a contiguous range of items
+        const uint32_t per = gridDim.x / 8u / (uint32_t)nsub2;
+        t = item0 + xcd * per + seq;
+        if (t >= n_items) return;
+    }
     const int tx = (int)(t % (uint32_t)a.ntx);
     t /= (uint32_t)a.ntx;
     const int ty = (int)(t % (uint32_t)a.nty);
     t /= (uint32_t)a.nty;
     if constexpr (FORM != kFormBlock) {
-        __shared__ q32::Lds<SZ> lds[4];
+        __shared__ q32::Lds<SZ> lds;
         q32::field_block<SZ, STATS, SR, FORM == kFormAligned>(a, a.s_lo + (int)t, tx, ty, sub,
-                                                              lds[wv]);
+                                                              lds);
     } else {
-        __shared__ Stage<T> stage[4][kWave];
-        __shared__ T pend[4][fieldk::pend_elems<T, SZ>()];
-        __shared__ double line[4][fieldk::kLineVals * kWave];
-        fieldk::field_block<T, SZ, STATS, K, SR>(a, a.s_lo + (int)t, tx, ty, sub, stage[wv],
-                                                 pend[wv], line[wv]);
+        __shared__ Stage<T> stage[kWave];
+        __shared__ T pend[fieldk::pend_elems<T, SZ>()];
+        __shared__ double line[fieldk::kLineVals * kWave];
+        fieldk::field_block<T, SZ, STATS, K, SR>(a, a.s_lo + (int)t, tx, ty, sub, stage, pend,
+                                                 line);
     }
 }
 
@@ -111,63 +134,75 @@ __global__ __launch_bounds__(256) void k_bits_blk(const T* field, int32_t nk, in
     if (lane < 8 && c * 8 + lane < nbx) out[kb * (uint64_t)nbx + (uint64_t)(c * 8 + lane)] = word;
 }
 
+// A launch holds at most 2^25 workgroups (a grid's threads are counted in 32
+// bits); larger calls take several.
+constexpr uint32_t kMaxGroups = 1u << 25;
+
 template <typename T, int SZ, int K, bool SR, int FORM>
-lsl_status launch_tkp(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_t st) {
-    const unsigned blocks = (n_items + 3u) / 4u;
-    if (stats)
-        k_field<T, SZ, true, K, SR, FORM><<<blocks, 256, 0, st>>>(a, n_items);
-    else
-        k_field<T, SZ, false, K, SR, FORM><<<blocks, 256, 0, st>>>(a, n_items);
-    LSL_HIP(hipGetLastError());
+lsl_status launch_form(const FieldArgs& a, bool stats, const uint32_t* queue, uint32_t n_items,
+                       hipStream_t st) {
+    const uint32_t nsub2 = (uint32_t)(a.tile / kBlockPix) * (uint32_t)(a.tile / kBlockPix);
+    const uint32_t per_launch = kMaxGroups / nsub2 / 8u * 8u;
+    for (uint32_t i0 = 0; i0 < n_items; i0 += per_launch) {
+        const uint32_t n = n_items - i0 < per_launch ? n_items - i0 : per_launch;
+        const uint32_t blocks = (n + 7u) / 8u * 8u * nsub2;
+        if (stats)
+            k_field<T, SZ, true, K, SR, FORM><<<blocks, 64, 0, st>>>(a, queue, i0, i0 + n);
+        else
+            k_field<T, SZ, false, K, SR, FORM><<<blocks, 64, 0, st>>>(a, queue, i0, i0 + n);
+        LSL_HIP(hipGetLastError());
+    }
     return LSL_OK;
 }
 
 template <typename T, int SZ, int K, bool SR>
-lsl_status launch_tk(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_t st) {
+lsl_status launch_tk(const FieldArgs& a, bool stats, const uint32_t* queue, uint32_t n,
+                     hipStream_t st) {
     if constexpr (std::is_same<T, float>::value && K == LSL_KERNEL_QUARTIC) {
         if constexpr (SZ >= 8) {
             if (field_form(a, SZ) == kFormAligned)
-                return launch_tkp<T, SZ, K, SR, kFormAligned>(a, stats, n_items, st);
+                return launch_form<T, SZ, K, SR, kFormAligned>(a, stats, queue, n, st);
         }
         if (field_form(a, SZ) != kFormBlock)
-            return launch_tkp<T, SZ, K, SR, kFormGeneral>(a, stats, n_items, st);
+            return launch_form<T, SZ, K, SR, kFormGeneral>(a, stats, queue, n, st);
     }
-    return launch_tkp<T, SZ, K, SR, kFormBlock>(a, stats, n_items, st);
+    return launch_form<T, SZ, K, SR, kFormBlock>(a, stats, queue, n, st);
 }
 
 template <typename T, int SZ>
-lsl_status launch_t(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_t st) {
+lsl_status launch_t(const FieldArgs& a, bool stats, const uint32_t* queue, uint32_t n,
+                    hipStream_t st) {
     if (a.kernel == LSL_KERNEL_GAUSS)
-        return a.strut_R ? launch_tk<T, SZ, LSL_KERNEL_GAUSS, true>(a, stats, n_items, st)
-                         : launch_tk<T, SZ, LSL_KERNEL_GAUSS, false>(a, stats, n_items, st);
-    return a.strut_R ? launch_tk<T, SZ, LSL_KERNEL_QUARTIC, true>(a, stats, n_items, st)
-                     : launch_tk<T, SZ, LSL_KERNEL_QUARTIC, false>(a, stats, n_items, st);
+        return a.strut_R ? launch_tk<T, SZ, LSL_KERNEL_GAUSS, true>(a, stats, queue, n, st)
+                         : launch_tk<T, SZ, LSL_KERNEL_GAUSS, false>(a, stats, queue, n, st);
+    return a.strut_R ? launch_tk<T, SZ, LSL_KERNEL_QUARTIC, true>(a, stats, queue, n, st)
+                     : launch_tk<T, SZ, LSL_KERNEL_QUARTIC, false>(a, stats, queue, n, st);
 }
 
 template <typename T>
-lsl_status launch_dt(const FieldArgs& a, bool stats, uint32_t n_items, hipStream_t st) {
+lsl_status launch_dt(const FieldArgs& a, bool stats, const uint32_t* queue, uint32_t n,
+                     hipStream_t st) {
     switch (slab_planes(a.slab, a.nk)) {
-        case 1: return launch_t<T, 1>(a, stats, n_items, st);
-        case 2: return launch_t<T, 2>(a, stats, n_items, st);
-        case 4: return launch_t<T, 4>(a, stats, n_items, st);
-        case 8: return launch_t<T, 8>(a, stats, n_items, st);
-        default: return launch_t<T, 16>(a, stats, n_items, st);
+        case 1: return launch_t<T, 1>(a, stats, queue, n, st);
+        case 2: return launch_t<T, 2>(a, stats, queue, n, st);
+        case 4: return launch_t<T, 4>(a, stats, queue, n, st);
+        case 8: return launch_t<T, 8>(a, stats, queue, n, st);
+        default: return launch_t<T, 16>(a, stats, queue, n, st);
     }
 }
 
 }  // namespace
 
-lsl_status launch_field(int dtype, const FieldArgs& a, bool stats, hipStream_t st) {
-    const int nsub = a.tile / kBlockPix;
-    const uint64_t n_items = (uint64_t)(a.s_hi - a.s_lo + 1) * (uint64_t)a.ntx * (uint64_t)a.nty *
-                             (uint64_t)(nsub * nsub);
+lsl_status launch_field(int dtype, const FieldArgs& a, bool stats, const uint32_t* queue,
+                        hipStream_t st) {
+    const uint64_t n_items = (uint64_t)(a.s_hi - a.s_lo + 1) * (uint64_t)a.ntx * (uint64_t)a.nty;
     if (n_items == 0 || a.nk <= 0) return LSL_OK;
-    if (n_items > 0xfffffff0ull) {
+    if (n_items > 0x7fffffffull) {               // (a slab group has fewer buckets)
         set_error("slice_field: too many work items in one launch");
         return LSL_EINTERNAL;
     }
-    if (dtype == LSL_F32) return launch_dt<float>(a, stats, (uint32_t)n_items, st);
-    return launch_dt<double>(a, stats, (uint32_t)n_items, st);
+    return dtype == LSL_F32 ? launch_dt<float>(a, stats, queue, (uint32_t)n_items, st)
+                            : launch_dt<double>(a, stats, queue, (uint32_t)n_items, st);
 }
 
 lsl_status launch_bits_blk(int dtype, const void* field, int32_t nk, int32_t W, int32_t H,

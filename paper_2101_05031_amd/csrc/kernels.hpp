@@ -147,8 +147,8 @@ struct FieldArgs {
 // that holds the planes a call evaluates in any slab.  A call for fewer
 // planes than a slab holds takes the smaller kernel (the field does not
 // depend on the choice): fewer registers and less LDS per wave, and no passes
-// over planes outside the range.  One plane of 2048^2 of 463k struts:
-// SZ_MEASURED.
+// over planes outside the range.  One plane of 2048^2 of 463k struts in slabs
+// of 8: 181 us with the kernel for 8 planes, 114 us with the one for 1.
 inline int slab_planes(int32_t slab, int32_t nk) {
     const int32_t m = slab < nk ? slab : nk;
     return m <= 1 ? 1 : m <= 2 ? 2 : m <= 4 ? 4 : m <= 8 ? 8 : 16;
@@ -162,7 +162,10 @@ inline int field_form(const FieldArgs& a, int SZ) {
     if (a.plane_ref) return kFormBlock;
     return a.slab == SZ && a.slab % 8 == 0 ? kFormAligned : kFormGeneral;
 }
-lsl_status launch_field(int dtype, const FieldArgs& a, bool stats, hipStream_t st);
+// queue: the (slab, tile) items in the order to take them (launch_queue_build),
+// or null.
+lsl_status launch_field(int dtype, const FieldArgs& a, bool stats, const uint32_t* queue,
+                        hipStream_t st);
 // Block-major binary image (see FieldArgs::bits_blk) of a field.
 lsl_status launch_bits_blk(int dtype, const void* field, int32_t nk, int32_t W, int32_t H,
                            double C, uint64_t* bits_blk, hipStream_t st);
@@ -247,17 +250,9 @@ lsl_status launch_node_offsets(const uint32_t* sorted_keys, size_t n, int64_t n_
                                uint32_t* node_off, hipStream_t st);
 
 // ---------------------------------------------------------------- batch.hip
-struct BatchArgs {
-    FieldArgs f;
-    const uint32_t* queue;            // items (s_rel, tile) in cost order
-    uint32_t n_items;
-    uint32_t* counter;                // device work counter (zeroed per launch)
-};
 lsl_status launch_queue_build(const FieldArgs& f, uint32_t* keys, uint32_t* vals,
                               uint32_t* keys_alt, uint32_t* vals_alt, uint32_t n_items,
                               uint32_t* tmp, const uint32_t** queue_out, hipStream_t st);
-// The caller zeroes a.counter before the launch.
-lsl_status launch_persistent(int dtype, const BatchArgs& a, hipStream_t st);
 
 // ---------------------------------------------------------------- support.hip
 // Self-support metrics (Sec. 5.2, Eqs. 11-14) and dGamma/dv.
