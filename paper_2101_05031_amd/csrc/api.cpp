@@ -282,6 +282,7 @@ struct lattice_bins {
     double R = 0, C = 0;
     bool strut_R = false;              // per-strut supports (in rec[].pad)
     bool plane_ref = false;            // float32 field: every plane its own reference
+    bool gauss_short = false;          // float32 Gaussian with supports within kGaussNear sigma
     bool wide = false;                 // float32 adjoint: 16x16-pixel regions
     int32_t wexp = 0;                  // float32 field: sums times 2^(5 wexp)
     float* rho = nullptr;              // float32 field: per-strut length scale
@@ -629,6 +630,7 @@ FieldArgs field_args(const lattice_bins* b, int32_t k0, int32_t nk, void* field)
         a.gk1 = 1.0 / (b->sigma * std::sqrt(2.0));
         a.gk2 = 1.0 / (2.0 * b->sigma * b->sigma);
         a.gc0 = b->sigma * std::sqrt(std::acos(-1.0) / 2.0);
+        a.gauss_short = b->gauss_short ? 1 : 0;
     }
     a.C = b->C;
     a.field = field;
@@ -754,7 +756,7 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
     const size_t En = std::max<size_t>(E, 1);
     if ((s = b->alloc_t(&klo, En)) || (s = b->alloc_t(&vals, En)) || (s = b->alloc_t(&ka, En)) ||
         (s = b->alloc_t(&va, En)) || (s = b->alloc_t(&rid, En)) || (s = b->alloc_t(&prid, En)) ||
-        (s = b->alloc_t(&cnt, 2 * (size_t)ns + 4)) || (s = b->alloc_t(&diff, 2 * ((size_t)ns + 1))) ||
+        (s = b->alloc_t(&cnt, 2 * (size_t)ns + 5)) || (s = b->alloc_t(&diff, 2 * ((size_t)ns + 1))) ||
         (s = b->alloc_t(&stmp, radix_tmp_elems(En))))
         return fail(s);
     if (L->dtype == LSL_F64 && (s = b->alloc_t(&khi, En))) return fail(s);
@@ -764,8 +766,8 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
     uint32_t* cnt_lo = cnt;
     uint32_t* cnt_hi = cnt + ns;
     uint32_t* counters = cnt + 2 * ns;   // [0] n_binned, [1] err, [2] ~smallest support,
-                                         // [3] largest r R
-    if ((s = fill_u32(cnt, 0u, 2 * (size_t)ns + 4, st)) ||
+                                         // [3] largest r R, [4] a support is far over sigma
+    if ((s = fill_u32(cnt, 0u, 2 * (size_t)ns + 5, st)) ||
         (s = fill_bytes0(diff, 2 * ((size_t)ns + 1) * 8, st)))
         return fail(s);
     PrepArgs pa{};
@@ -804,6 +806,7 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
     pa.key_s0 = ks0;
     pa.max_r_over_sigma = L->kernel == LSL_KERNEL_GAUSS ? kMaxROverSigma : 0.0;
     pa.sigma = L->sigma;
+    pa.far = counters + 4;
     pa.keep_zero = L->keep_zero_weight ? 1 : 0;
     if ((s = launch_prep(L->dtype, pa, st))) return fail(s);
 
@@ -844,7 +847,7 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
     }
 
     // read the plan back
-    std::vector<uint32_t> h_cnt(2 * (size_t)ns + 4);
+    std::vector<uint32_t> h_cnt(2 * (size_t)ns + 5);
     std::vector<unsigned long long> h_diff((size_t)ns + 1);
     std::vector<uint32_t> h_rdiff((size_t)ns + 1);
     hipError_t he = hipMemcpyAsync(h_cnt.data(), cnt, h_cnt.size() * 4, hipMemcpyDeviceToHost, st);
@@ -870,6 +873,7 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
         return fail(LSL_EINVAL);
     }
     b->n_binned = h_cnt[2 * ns];
+    b->gauss_short = L->kernel == LSL_KERNEL_GAUSS && L->dtype == LSL_F32 && h_cnt[2 * ns + 4] == 0u;
     {
         // The float32 field kernel shares one reference plane among 8 planes
         // when the shift it applies stays small against the support:
@@ -929,6 +933,7 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
         ga.support = L->support;
         ga.kernel = L->kernel;
         ga.sigma = L->sigma;
+        ga.wq_unit = b->gauss_short ? L->sigma * std::sqrt(2.0) : 1.0;
         ga.rec = b->rec;
         ga.ranges = b->ranges;
         ga.pranges = b->pranges;
@@ -1418,7 +1423,7 @@ BackArgs back_args(const lattice_bins* b, int g, int32_t k0, int32_t nk, int s_l
 // What decides the kernels a slab group's graphs record (the cached graphs
 // of one shape differ only in launch arguments).
 struct GraphShape {
-    int32_t dtype, kernel, strut_R, plane_ref, slab, planes, tile, phase;
+    int32_t dtype, kernel, gauss_short, strut_R, plane_ref, slab, planes, tile, phase;
     int32_t field, bits, segs, slot;
 };
 
@@ -1646,7 +1651,7 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
         // the captures took host time: the group's binning stage ends here
         if (cs == LSL_OK && hipEventRecord(ev[1], st) != hipSuccess) cs = LSL_EDEVICE;
         for (int ph = 0; ph < 3 && cs == LSL_OK; ++ph) {
-            GraphShape shape{b->dtype,   b->kernel,        b->strut_R ? 1 : 0,
+            GraphShape shape{b->dtype, b->kernel, b->gauss_short ? 1 : 0, b->strut_R ? 1 : 0,
                              b->plane_ref ? 1 : 0, b->slab, planes, b->tile, ph,
                              field ? 1 : 0, bits ? 1 : 0, capacity > 0 ? 1 : 0,
                              (int32_t)((n_call_groups - 1) & 1)};

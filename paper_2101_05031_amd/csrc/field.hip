@@ -172,6 +172,12 @@ lsl_status launch_tk(const FieldArgs& a, bool stats, const uint32_t* queue, uint
 template <typename T, int SZ>
 lsl_status launch_t(const FieldArgs& a, bool stats, const uint32_t* queue, uint32_t n,
                     hipStream_t st) {
+    if constexpr (std::is_same<T, float>::value) {
+        if (a.kernel == LSL_KERNEL_GAUSS && a.gauss_short)
+            return a.strut_R
+                       ? launch_tk<T, SZ, fieldk::kGaussShort, true>(a, stats, queue, n, st)
+                       : launch_tk<T, SZ, fieldk::kGaussShort, false>(a, stats, queue, n, st);
+    }
     if (a.kernel == LSL_KERNEL_GAUSS)
         return a.strut_R ? launch_tk<T, SZ, LSL_KERNEL_GAUSS, true>(a, stats, queue, n, st)
                          : launch_tk<T, SZ, LSL_KERNEL_GAUSS, false>(a, stats, queue, n, st);

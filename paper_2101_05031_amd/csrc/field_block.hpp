@@ -1,5 +1,5 @@
-// Per-block field evaluation shared by the plain and the persistent field
-// kernels (see field.hip for the method).
+// Per-block field evaluation of the general field kernel (see field.hip for
+// the method).
 #pragma once
 
 #include "kernels.hpp"
@@ -79,6 +79,57 @@ __device__ __forceinline__ T eval_term_gauss(const Stage<T>& e, T dX, T dY, T d2
     return e.wq * N::fma_(N::exp_(H * k2) * c0, E, ca - cb);
 }
 
+// The Gaussian term of lattices whose supports stay within kGaussNear sigma
+// (3 sigma is the usual choice), in float32.  Lengths are in units of
+// sigma sqrt 2 (the staging scales them in float64), so that H is the
+// exponent itself and the ends the erf's arguments, |x| <= h <= 2.143:
+//
+//   wq [exp(H) (F(cb) - F(ca)) - (cb - ca)],  F(x) = integral of exp(-t^2)
+//   from 0 to x = x P(x^2),
+//
+// with P of degree 9 about x^2 = 2.3 (minimax fit of F(x)/x on x^2 <= 4.6,
+// relative error 2.3e-8; in float32 the error of F is at most 1.1e-7, 2.7e-8
+// in the mean square), and exp(H) = 2^t (1 + l ln 2), t + l = H log2 e in two
+// parts, from the hardware's exp2.  No branches, where erff takes both of its
+// own in most waves; bound by its instructions' issue.  16 planes of 2048^2
+// of 1M struts: 4.3 ms with erff and expf, 2.75 ms so.
+constexpr int kGaussShort = 2;                  // the kernel parameter of this form
+
+__device__ __forceinline__ float gauss_integral(float x) {
+    const float t = __builtin_fmaf(x, x, -2.3f);
+    float p = -1.9834541e-08f;
+    p = __builtin_fmaf(p, t, 2.1390387e-07f);
+    p = __builtin_fmaf(p, t, -1.7929643e-06f);
+    p = __builtin_fmaf(p, t, 1.5054211e-05f);
+    p = __builtin_fmaf(p, t, -0.00011398175f);
+    p = __builtin_fmaf(p, t, 0.00075566163f);
+    p = __builtin_fmaf(p, t, -0.0043729343f);
+    p = __builtin_fmaf(p, t, 0.022094995f);
+    p = __builtin_fmaf(p, t, -0.10117798f);
+    p = __builtin_fmaf(p, t, 0.56567758f);
+    return x * p;
+}
+
+__device__ __forceinline__ float gauss_exp(float H) {
+    const float t = H * 1.44269502f;
+    const float l = __builtin_fmaf(H, 1.92596303e-8f, __builtin_fmaf(H, 1.44269502f, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    return __builtin_fmaf(e, l * 0.693147182f, e);
+}
+
+__device__ __forceinline__ float eval_term_short(const Stage<float>& e, float dX, float dY,
+                                                 float d2) {
+    using N = Num<float>;
+    const float du = N::fma_(dX, e.ux, dY * e.uy);
+    const float al = e.ntc - du;
+    const float be = e.nbtc - du;
+    const float H = N::fma_(du, du, N::fma_(e.mx2, dX, N::fma_(e.my2, dY, e.H0 - d2)));
+    const float h = N::sqrt_(N::max_(H, 0.0f));
+    const float ca = N::clamp_(al, -h, h);
+    const float cb = N::clamp_(be, -h, h);
+    return e.wq * N::fma_(gauss_exp(H), gauss_integral(cb) - gauss_integral(ca), ca - cb);
+}
+
 template <typename T>
 __device__ __forceinline__ void comp_add(T t, T& s, T& c) {
     const T sn = s + t;
@@ -117,12 +168,16 @@ constexpr int kLineVals = 6;
 // One wave evaluates the 8x8 block `sub` of tile (tx, ty) over the planes of
 // `slab` that lie in [k0, k0+nk); `stage` is the wave's 64-entry LDS area,
 // `pend` its pend_elems<T, SZ>() open-run sums and `line` its
-// kLineVals * 64 line values.  K: LSL_KERNEL_QUARTIC or LSL_KERNEL_GAUSS;
+// kLineVals * 64 line values.  K: LSL_KERNEL_QUARTIC, LSL_KERNEL_GAUSS
+// or kGaussShort;
 // SR: per-strut supports (in the record's pad) instead of one support R.
 template <typename T, int SZ, bool STATS, int K, bool SR>
 __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx, int ty, int sub,
                                             Stage<T>* stage, T* pend, double* line) {
-    constexpr int G = K == LSL_KERNEL_GAUSS ? 1 : Group<T>::n;
+    constexpr bool kShort = K == kGaussShort;
+    constexpr int G = K == LSL_KERNEL_QUARTIC ? Group<T>::n : 1;
+    // the unit of length is 1 / lu (1, or sigma sqrt 2)
+    const double lu = kShort ? a.gk1 : 1.0;
     const int lane = lane_id();
     const uint32_t n_binned = a.n_binned, n_pairs = a.n_pairs;
     const int nsub = a.tile / kBlockPix;
@@ -145,8 +200,8 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
     const bool pix = pi < a.W && pj < a.H;
     const double cx = a.x0 + ((double)i0 + 4.0) * a.dx;     // centre of the 8x8 centres
     const double cy = a.y0 + ((double)j0 + 4.0) * a.dy;
-    const T dX = (T)(((double)lx - 3.5) * a.dx);
-    const T dY = (T)(((double)ly - 3.5) * a.dy);
+    const T dX = (T)(((double)lx - 3.5) * a.dx * lu);
+    const T dY = (T)(((double)ly - 3.5) * a.dy * lu);
     const T d2 = dX * dX + dY * dY;
     // half extents of the block's pixel centres about c
     const double hx = 3.5 * a.dx, hy = 3.5 * a.dy;
@@ -238,13 +293,13 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
                 if (mask == 0ull) continue;
                 if (pass) {
                     Stage<T> s;
-                    s.mx2 = (T)(2.0 * mx);
-                    s.my2 = (T)(2.0 * my);
+                    s.mx2 = (T)(2.0 * mx * lu);
+                    s.my2 = (T)(2.0 * my * lu);
                     s.ux = (T)ux;
                     s.uy = (T)uy;
-                    s.ntc = (T)(-tc);
-                    s.nbtc = (T)(L - tc);
-                    s.H0 = (T)(R2 - m2);
+                    s.ntc = (T)(-tc * lu);
+                    s.nbtc = (T)((L - tc) * lu);
+                    s.H0 = (T)((R2 - m2) * (lu * lu));
                     s.wq = r.wq;
                     // rank among the passing lanes: set bits of mask below this lane
                     const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
@@ -255,9 +310,13 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
                 const int n = __popcll(mask);
                 T s_ = acc_s[k], c_ = acc_c[k];
                 auto term_at = [&](int j) -> T {
-                    const T t = K == LSL_KERNEL_GAUSS
-                                    ? eval_term_gauss<T>(stage[j], dX, dY, d2, gk1, gk2, gc0)
-                                    : eval_term<T>(stage[j], dX, dY, d2);
+                    T t;
+                    if constexpr (kShort)
+                        t = eval_term_short(stage[j], dX, dY, d2);
+                    else if constexpr (K == LSL_KERNEL_GAUSS)
+                        t = eval_term_gauss<T>(stage[j], dX, dY, d2, gk1, gk2, gc0);
+                    else
+                        t = eval_term<T>(stage[j], dX, dY, d2);
                     if (STATS) n_useful += t > T(0) ? 1ull : 0ull;
                     return t;
                 };

@@ -5,6 +5,10 @@
 
 namespace lsl {
 
+// The float32 Gaussian kernel's short form holds up to this support over
+// sigma: its fit of the erf ends at x^2 = 4.6, R / sigma = 3.033.
+constexpr double kGaussNear = 3.03;
+
 // ----------------------------------------------------------------- prep.hip
 struct PrepArgs {
     const void* nodes;
@@ -35,6 +39,7 @@ struct PrepArgs {
     const void* support;              // [n_edges] per-strut supports, or null (R for all)
     uint32_t* key_s0;                 // [n_edges] first slab (n_slabs if not binned), or null
     double max_r_over_sigma;          // > 0: reject supports above this many sigma
+    uint32_t* far;                    // set to 1 if a binned support is above kGaussNear sigma
     double sigma;
     int32_t keep_zero;                // 1: bin struts of weight 0 too
 };
@@ -52,6 +57,7 @@ struct GatherArgs {
     const void* support;              // per-strut supports or null
     int32_t kernel;                   // LSL_KERNEL_*
     double sigma;
+    double wq_unit;                   // Gaussian: factor of the folded weight
     void* rec;                        // StrutRec<T> [n_binned]; pad holds R_j with supports
     SRange* ranges;                   // [n_binned]
     PRange* pranges;                  // [n_binned]
@@ -135,6 +141,8 @@ struct FieldArgs {
     int32_t strut_R;                  // 1: strut j's support is rec[j].pad, else R
     int32_t kernel;                   // LSL_KERNEL_*
     double gk1, gk2, gc0;             // Gaussian: 1/(sigma sqrt 2), 1/(2 sigma^2), sigma sqrt(pi/2)
+    int32_t gauss_short;              // float32 Gaussian: 1 = supports within kGaussNear sigma
+                                      // (lengths and weights in units of sigma sqrt 2)
     int32_t plane_ref;                // float32 quartic: 1 = every plane is its own
                                       // reference plane (field_q32.hpp), 0 = groups of 8
     void* field;                      // [nk][H][W] or null (not written)

@@ -130,6 +130,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(PrepArgs a) {
                     if (rz.ok && rx.ok && ry.ok) {
                         binned = true;
                         rs_binned = (float)Rs;
+                        if (a.max_r_over_sigma > 0.0 && Rs > kGaussNear * a.sigma) *a.far = 1u;
                         wr_binned = (float)((double)w * Rs);
                         pr.i0 = (uint16_t)rx.i0;
                         pr.i1 = (uint16_t)rx.i1;
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(256) void k_gather(GatherArgs a) {
     r.az = nd[3 * ia + 2];
     // the weight folded with the kernel's constant: r / R^4 (Eq. 5), or
     // r exp(-R^2 / 2 sigma^2) (Gaussian)
-    r.wq = a.kernel == LSL_KERNEL_GAUSS ? (T)(w * exp(-R2 / (2.0 * a.sigma * a.sigma)))
+    r.wq = a.kernel == LSL_KERNEL_GAUSS ? (T)(w * exp(-R2 / (2.0 * a.sigma * a.sigma)) * a.wq_unit)
                                         : (T)(w / (R2 * R2));
     r.bx = nd[3 * ib];
     r.by = nd[3 * ib + 1];

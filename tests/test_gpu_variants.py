@@ -227,3 +227,24 @@ def test_per_strut_supports_through_autograd_and_matching():
     w1, hist = tuning.match_density(n, e, w, lat.R, lat.C, grid, target, vx, vy, vz, iters=8,
                                     lr=0.05 * float(w.mean()), support=sup)
     assert min(h["loss"] for h in hist) < 0.3 * hist[0]["loss"]
+
+
+@pytest.mark.parametrize("per_strut", [False, True])
+@pytest.mark.parametrize("ratio", [0.5, 3.0, 3.029, 3.031, 6.0, 11.9])
+def test_gauss_widths_around_the_short_form(ratio, per_strut):
+    """Supports of up to ratio sigma, on both sides of the float32 kernel's
+    short form (3.03): the same tolerance as for every float32 field."""
+    lat, grid = small_kuhn()
+    if per_strut:
+        lat = synth.with_supports(lat)
+        top = float(lat.support.max())
+    else:
+        top = lat.R
+    sigma = top / ratio
+    sup = lat.support.astype(np.float64) if per_strut else lat.R
+    w = synth.weight_for_radius_gauss(np.asarray(lat.radius, np.float64), sup, sigma, lat.C)
+    lat = dataclasses.replace(lat, weight=w.astype(np.float32), kernel="gauss", sigma=sigma)
+    ks = range(9, 13)
+    b = bin_lattice(lat, grid, slab=4)
+    f = api.slice_field(b, ks.start, len(ks))
+    assert_field_close(f.cpu().numpy(), oracle_field(lat, grid, ks), lat.C, 1e-5, "gauss width")
