@@ -361,7 +361,7 @@ struct lattice_bins {
     size_t n_back = 0;
     double last_field_ms = -1.0, last_group_bin_ms = -1.0, last_queue_ms = -1.0,
            last_contour_ms = -1.0;
-    bool queue_in_alt = false;      // the sorted work queue is in the alternate buffer
+    const uint32_t* queue = nullptr;   // the sorted work queue (in queue_buf)
 
     ~lattice_bins() {
         hipDeviceSynchronize();
@@ -1420,6 +1420,30 @@ BackArgs back_args(const lattice_bins* b, int g, int32_t k0, int32_t nk, int s_l
     return a;
 }
 
+// room for the work queue of the largest slab group
+lsl_status ensure_queue(lattice_bins* b, hipStream_t st) {
+    size_t max_items = 1;
+    for (auto& G : b->groups)
+        max_items = std::max<size_t>(max_items, (size_t)(G.sb - G.sa + 1) * b->ntx * b->nty);
+    if (b->queue_cap >= max_items) return LSL_OK;
+    LSL_HIP(hipStreamSynchronize(st));
+    b->release(b->queue_buf);
+    b->queue_buf = nullptr;
+    b->queue_cap = 0;
+    LSL_TRY(b->alloc_t(&b->queue_buf, 4 * max_items + 64 + radix_tmp_elems(max_items)));
+    b->queue_cap = max_items;
+    return LSL_OK;
+}
+
+// The (slab, tile) items of a.s_lo .. a.s_hi in descending cost order.
+lsl_status build_queue(lattice_bins* b, const FieldArgs& a, const uint32_t** queue,
+                       hipStream_t st) {
+    const uint32_t n = (uint32_t)((a.s_hi - a.s_lo + 1) * b->ntx * b->nty);
+    uint32_t* qk = b->queue_buf;
+    uint32_t *qv = qk + b->queue_cap, *qk2 = qv + b->queue_cap, *qv2 = qk2 + b->queue_cap;
+    return launch_queue_build(a, qk, qv, qk2, qv2, n, qv2 + b->queue_cap + 64, queue, st);
+}
+
 // What decides the kernels a slab group's graphs record (the cached graphs
 // of one shape differ only in launch arguments).
 struct GraphShape {
@@ -1453,21 +1477,9 @@ lsl_status batch_group_work(lattice_bins* b, int g, int32_t k0, int32_t nk, int 
     a.group_s0 = b->groups[g].sa;
     a.s_lo = s_lo;
     a.s_hi = s_hi;
-    const uint32_t n_items = (uint32_t)((s_hi - s_lo + 1) * b->ntx * b->nty);
-    uint32_t* qk = b->queue_buf;
-    uint32_t* qv = qk + b->queue_cap;
-    uint32_t* qk2 = qv + b->queue_cap;
-    uint32_t* qv2 = qk2 + b->queue_cap;
-    unsigned long long* base = (unsigned long long*)(qv2 + b->queue_cap);
-    uint32_t* qtmp = qv2 + b->queue_cap + 64;
-    if (phase == 0) {
-        const uint32_t* queue = nullptr;
-        LSL_TRY(launch_queue_build(a, qk, qv, qk2, qv2, n_items, qtmp, &queue, st));
-        b->queue_in_alt = queue != qv;
-        return LSL_OK;
-    }
-    if (phase == 1)
-        return launch_field(b->dtype, a, false, b->queue_in_alt ? qv2 : qv, st);
+    unsigned long long* base = (unsigned long long*)(b->queue_buf + 4 * b->queue_cap);
+    if (phase == 0) return build_queue(b, a, &b->queue, st);
+    if (phase == 1) return launch_field(b->dtype, a, false, b->queue, st);
     LSL_TRY(launch_contours_count(img, nkg, b->grid.W, b->grid.H, offsets + (kg0 - k0), nullptr,
                                   b->ctmp, base, st));
     LSL_TRY(launch_contours_emit(img, nkg, b->grid.W, b->grid.H, b->ctmp, base, segs, capacity,
@@ -1545,6 +1557,12 @@ lsl_status slice_field_backward(lattice_bins* b, int32_t k0, int32_t nk, const v
                 b->emi_group = g;
             }
             BackArgs a = back_args(b, g, k0, nk, s_lo, s_hi, grad_field);
+            LSL_TRY(ensure_queue(b, st));
+            FieldArgs fa = field_args(b, k0, nk, nullptr);
+            fa.group_s0 = G.sa;
+            fa.s_lo = s_lo;
+            fa.s_hi = s_hi;
+            LSL_TRY(build_queue(b, fa, &a.queue, st));
             if (b->back_events.size() <= b->n_back) {
                 lattice_bins::EvPair bp{};
                 for (auto& e : bp.ev) LSL_HIP(hipEventCreate(&e));
@@ -1593,20 +1611,11 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
     hipStream_t st = S(stream);
     const size_t plane = (size_t)b->grid.W * (size_t)b->grid.H;
     // scratch sized for the largest group
-    size_t max_items = 1, max_planes = 1;
-    for (auto& G : b->groups) {
-        max_items = std::max<size_t>(max_items, (size_t)(G.sb - G.sa + 1) * b->ntx * b->nty);
+    size_t max_planes = 1;
+    for (auto& G : b->groups)
         max_planes = std::max<size_t>(max_planes, (size_t)(G.sb - G.sa + 1) * b->slab);
-    }
     max_planes = std::min<size_t>(max_planes, (size_t)nk);
-    if (b->queue_cap < max_items) {
-        LSL_HIP(hipStreamSynchronize(st));
-        b->release(b->queue_buf);
-        b->queue_buf = nullptr;
-        b->queue_cap = 0;
-        LSL_TRY(b->alloc_t(&b->queue_buf, 4 * max_items + 64 + radix_tmp_elems(max_items)));
-        b->queue_cap = max_items;
-    }
+    LSL_TRY(ensure_queue(b, st));
     LSL_TRY(b->grow(&b->ctmp, &b->ctmp_elems,
                     contour_tmp_elems((int32_t)max_planes, b->grid.W, b->grid.H), st));
     LSL_TRY(ensure_cbits(b, (int32_t)max_planes, st));

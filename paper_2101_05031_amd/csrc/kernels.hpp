@@ -222,6 +222,7 @@ struct BackArgs {
     const double4* line;              // [n_binned]: u (x, y, z), L per strut (float64)
     int32_t plane_ref;                // 1: every plane its own reference (coarse plane pitch)
     int32_t wide;                     // float32: 1 = 16x16-pixel regions, 0 = 8x8
+    const uint32_t* queue;            // the (slab, tile) items in cost order
 };
 lsl_status launch_backward(int dtype, const BackArgs& a, hipStream_t st);
 
