@@ -144,6 +144,93 @@ lsl_status static_scratch(double** out) {
     return LSL_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Page-locked buffers for read-backs.  A copy into pageable memory takes the
+// runtime 15 us and more of the caller's time per call; page-locked memory
+// costs hundreds to allocate.  Up to kKeep small buffers are kept for the
+// next caller (each used by one call at a time); lsl_cache_trim frees them.
+// Larger read-backs use pageable memory.
+// ---------------------------------------------------------------------------
+class PinnedPool {
+  public:
+    static constexpr size_t kBytes = 64 * 1024, kKeep = 8;
+    static PinnedPool& get() {
+        static PinnedPool* p = new PinnedPool();     // never destroyed: no teardown at exit
+        return *p;
+    }
+    void* take() {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (!free_.empty()) {
+                void* p = free_.back();
+                free_.pop_back();
+                return p;
+            }
+        }
+        void* p = nullptr;
+        if (hipHostMalloc(&p, kBytes, hipHostMallocPortable) != hipSuccess) {
+            hipGetLastError();
+            return nullptr;
+        }
+        return p;
+    }
+    void give(void* p) {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (free_.size() < kKeep) {
+                free_.push_back(p);
+                return;
+            }
+        }
+        hipHostFree(p);
+    }
+    void trim() {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (void* p : free_) hipHostFree(p);
+        free_.clear();
+    }
+
+  private:
+    std::mutex mu_;
+    std::vector<void*> free_;
+};
+
+// Host memory for one read-back, for the length of a call.  The copies into
+// it have ended when it goes out of scope (the callers synchronise; a call that
+// failed in between synchronises here).
+struct HostBuf {
+    void* p = nullptr;
+    bool pinned = false;
+    std::vector<unsigned char> heap;
+    hipStream_t wait = nullptr;
+    bool pending = false;
+    lsl_status get(size_t bytes) {
+        if (bytes <= PinnedPool::kBytes) p = PinnedPool::get().take();
+        pinned = p != nullptr;
+        if (!pinned) {
+            heap.resize(bytes);
+            p = heap.data();
+        }
+        return LSL_OK;
+    }
+    // copies `bytes` from the device to this buffer and waits for it
+    hipError_t read(const void* src, size_t bytes, hipStream_t st) {
+        wait = st;
+        pending = true;
+        hipError_t e = hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) pending = false;
+        return e;
+    }
+    HostBuf() = default;
+    HostBuf(const HostBuf&) = delete;
+    HostBuf& operator=(const HostBuf&) = delete;
+    ~HostBuf() {
+        if (pending) hipStreamSynchronize(wait);
+        if (pinned) PinnedPool::get().give(p);
+    }
+};
+
 }  // namespace lsl
 
 using namespace lsl;
@@ -362,6 +449,7 @@ struct lattice_bins {
     double last_field_ms = -1.0, last_group_bin_ms = -1.0, last_queue_ms = -1.0,
            last_contour_ms = -1.0;
     const uint32_t* queue = nullptr;   // the sorted work queue (in queue_buf)
+    hipStream_t cap = nullptr;         // capture stream of slice_batch over several groups
 
     ~lattice_bins() {
         hipDeviceSynchronize();
@@ -371,6 +459,7 @@ struct lattice_bins {
         for (auto& bp : back_events)
             for (auto& e : bp.ev)
                 if (e) hipEventDestroy(e);
+        if (cap) hipStreamDestroy(cap);
         for (auto& a : allocs) DeviceCache::get().release(a.first, a.second);
     }
 
@@ -412,7 +501,7 @@ struct lattice_bins {
     template <typename T>
     lsl_status grow(T** p, size_t* cap, size_t need, hipStream_t st) {
         if (need <= *cap) return LSL_OK;
-        LSL_HIP(hipStreamSynchronize(st));
+        if (*p) LSL_HIP(hipStreamSynchronize(st));
         release(*p);
         *p = nullptr;
         *cap = 0;
@@ -754,22 +843,26 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
     PRange* prid = nullptr;
     unsigned long long* diff = nullptr;
     const size_t En = std::max<size_t>(E, 1);
+    // the plan's histograms side by side, read back in one copy: pair
+    // differences, cell differences, struts per first and last slab, counters
+    void* plan = nullptr;
+    const size_t plan_bytes = ((size_t)ns + 1) * 8 + ((size_t)ns + 1) * 4 + (2 * (size_t)ns + 5) * 4;
     if ((s = b->alloc_t(&klo, En)) || (s = b->alloc_t(&vals, En)) || (s = b->alloc_t(&ka, En)) ||
         (s = b->alloc_t(&va, En)) || (s = b->alloc_t(&rid, En)) || (s = b->alloc_t(&prid, En)) ||
-        (s = b->alloc_t(&cnt, 2 * (size_t)ns + 5)) || (s = b->alloc_t(&diff, 2 * ((size_t)ns + 1))) ||
+        (s = b->alloc(&plan, plan_bytes)) ||
         (s = b->alloc_t(&stmp, radix_tmp_elems(En))))
         return fail(s);
     if (L->dtype == LSL_F64 && (s = b->alloc_t(&khi, En))) return fail(s);
     // per-strut supports: first-slab keys by edge id, then the gathered keys
     // and one alternate key/value pair for their sort
     if (L->support && (s = b->alloc_t(&ks0, 3 * En))) return fail(s);
+    diff = (unsigned long long*)plan;
+    cnt = (uint32_t*)(diff + ns + 1) + ns + 1;
     uint32_t* cnt_lo = cnt;
     uint32_t* cnt_hi = cnt + ns;
-    uint32_t* counters = cnt + 2 * ns;   // [0] n_binned, [1] err, [2] ~smallest support,
+    uint32_t* counters = cnt + 2 * ns;   // (behind cnt_hi) [0] n_binned, [1] err, [2] ~smallest support,
                                          // [3] largest r R, [4] a support is far over sigma
-    if ((s = fill_u32(cnt, 0u, 2 * (size_t)ns + 5, st)) ||
-        (s = fill_bytes0(diff, 2 * ((size_t)ns + 1) * 8, st)))
-        return fail(s);
+    if ((s = fill_u32((uint32_t*)plan, 0u, plan_bytes / 4, st))) return fail(s);
     PrepArgs pa{};
     pa.nodes = L->nodes;
     pa.edges = L->edges;
@@ -847,20 +940,18 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
     }
 
     // read the plan back
-    std::vector<uint32_t> h_cnt(2 * (size_t)ns + 5);
-    std::vector<unsigned long long> h_diff((size_t)ns + 1);
-    std::vector<uint32_t> h_rdiff((size_t)ns + 1);
-    hipError_t he = hipMemcpyAsync(h_cnt.data(), cnt, h_cnt.size() * 4, hipMemcpyDeviceToHost, st);
-    if (he == hipSuccess)
-        he = hipMemcpyAsync(h_diff.data(), diff, h_diff.size() * 8, hipMemcpyDeviceToHost, st);
-    if (he == hipSuccess)
-        he = hipMemcpyAsync(h_rdiff.data(), diff + ns + 1, h_rdiff.size() * 4,
-                            hipMemcpyDeviceToHost, st);
-    if (he == hipSuccess) he = hipStreamSynchronize(st);
+    HostBuf hb;
+    if ((s = hb.get(plan_bytes))) return fail(s);
+    hipError_t he = hb.read(plan, plan_bytes, st);
     if (he != hipSuccess) {
         set_error(std::string("lattice_bin: ") + hipGetErrorString(he));
         return fail(LSL_EDEVICE);
     }
+    const unsigned long long* hd = (const unsigned long long*)hb.p;
+    const uint32_t* hr = (const uint32_t*)(hd + ns + 1);
+    const std::vector<unsigned long long> h_diff(hd, hd + ns + 1);
+    const std::vector<uint32_t> h_rdiff(hr, hr + ns + 1);
+    const std::vector<uint32_t> h_cnt(hr + ns + 1, hr + ns + 1 + 2 * (size_t)ns + 5);
     const uint32_t err = h_cnt[2 * ns + 1];
     if (err) {
         std::string m = "lattice_bin:";
@@ -916,15 +1007,11 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
         (s = b->alloc_t(&b->line, nb)) || (s = b->alloc_t(&b->rho, nb)))
         return fail(s);
     if (b->n_binned) {
-        he = hipMemcpyAsync(b->perm, perm_src, (size_t)b->n_binned * 4, hipMemcpyDeviceToDevice, st);
-        if (he != hipSuccess) {
-            set_error(std::string("lattice_bin: ") + hipGetErrorString(he));
-            return fail(LSL_EDEVICE);
-        }
         GatherArgs ga{};
         ga.nodes = L->nodes;
         ga.edges = L->edges;
         ga.weight = L->weight;
+        ga.perm_src = perm_src;
         ga.perm = b->perm;
         ga.ranges_by_id = rid;
         ga.pranges_by_id = prid;
@@ -950,7 +1037,7 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
         return fail(LSL_EDEVICE);
     }
     for (void* p : {(void*)klo, (void*)khi, (void*)vals, (void*)ka, (void*)va, (void*)rid,
-                    (void*)prid, (void*)cnt, (void*)diff, (void*)stmp, (void*)ks0})
+                    (void*)prid, plan, (void*)stmp, (void*)ks0})
         b->release(p);
 
     // ---- resident-group buffers sized for the largest group
@@ -1051,11 +1138,11 @@ lsl_status lattice_support(const lsl_lattice* L, const double* print_dir, lsl_su
     }
     LSL_TRY(fill_u32((uint32_t*)a.err, 0u, 1, st));
     LSL_TRY(launch_support(L->dtype, a, st));
-    double h[6] = {0, 0, 0, 0, 0, 0};
-    int herr = 0;
-    LSL_HIP(hipMemcpyAsync(h, a.sums, 5 * sizeof(double), hipMemcpyDeviceToHost, st));
-    LSL_HIP(hipMemcpyAsync(&herr, a.err, sizeof(int), hipMemcpyDeviceToHost, st));
-    LSL_HIP(hipStreamSynchronize(st));
+    HostBuf hb;                                   // the sums, then the error flag
+    LSL_TRY(hb.get(7 * sizeof(double)));
+    LSL_HIP(hb.read(a.sums, 7 * sizeof(double), st));
+    const double* h = (const double*)hb.p;
+    const int herr = *(const int*)(h + 6);
     LSL_CHECK(herr == 0, "edge index out of range");
     out->risky_area = h[0];
     out->area = h[1];
@@ -1072,6 +1159,7 @@ lsl_status lsl_cache_trim(int64_t* cached_bytes) {
     if (cached_bytes) *cached_bytes = (int64_t)DeviceCache::get().cached();
     const lsl_status gs = GraphCache::get().trim();
     DeviceCache::get().trim();
+    PinnedPool::get().trim();
     return gs;
 }
 
@@ -1231,9 +1319,10 @@ lsl_status slice_contours(const lattice_bins* cb, int32_t nk, const void* field,
                             (uint64_t*)b->cbits, st));
     LSL_TRY(launch_contours_count(img, nk, b->grid.W, b->grid.H, offsets, case_codes, b->ctmp,
                                   nullptr, st));
-    int64_t tot = 0;
-    LSL_HIP(hipMemcpyAsync(&tot, offsets + nk, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    LSL_HIP(hipStreamSynchronize(st));
+    HostBuf hb;
+    LSL_TRY(hb.get(sizeof(int64_t)));
+    LSL_HIP(hb.read(offsets + nk, sizeof(int64_t), st));
+    const int64_t tot = *(const int64_t*)hb.p;
     if (total) *total = tot;
     if (tot > capacity) {
         set_error("slice_contours: " + std::to_string(tot) + " segments exceed capacity " +
@@ -1266,9 +1355,10 @@ lsl_status slice_polylines(const lattice_bins* cb, int32_t nk, const void* field
                             (uint64_t*)b->cbits, st));
     LSL_TRY(launch_contours_count(img, nk, b->grid.W, b->grid.H, offsets, nullptr, b->ctmp,
                                   nullptr, st));
-    std::vector<int64_t> h_off((size_t)nk + 1);
-    LSL_HIP(hipMemcpyAsync(h_off.data(), offsets, h_off.size() * 8, hipMemcpyDeviceToHost, st));
-    LSL_HIP(hipStreamSynchronize(st));
+    HostBuf hb;
+    LSL_TRY(hb.get(((size_t)nk + 1) * 8));
+    LSL_HIP(hb.read(offsets, ((size_t)nk + 1) * 8, st));
+    const int64_t* h_off = (const int64_t*)hb.p;
     const int64_t tot = h_off[nk];
     if (total) *total = tot;
     if (tot > capacity) {
@@ -1426,7 +1516,7 @@ lsl_status ensure_queue(lattice_bins* b, hipStream_t st) {
     for (auto& G : b->groups)
         max_items = std::max<size_t>(max_items, (size_t)(G.sb - G.sa + 1) * b->ntx * b->nty);
     if (b->queue_cap >= max_items) return LSL_OK;
-    LSL_HIP(hipStreamSynchronize(st));
+    if (b->queue_buf) LSL_HIP(hipStreamSynchronize(st));
     b->release(b->queue_buf);
     b->queue_buf = nullptr;
     b->queue_cap = 0;
@@ -1632,7 +1722,16 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
         b->last_field_ms = b->last_group_bin_ms = b->last_queue_ms = b->last_contour_ms = 0.0;
         return LSL_OK;
     }
-    hipStream_t cap = nullptr;
+    // The graphs spare a call of several groups the gaps between its launches.
+    // A call that touches one group has nothing to repeat, and recording,
+    // updating and launching its three graphs takes the host longer than the
+    // dozen launches (812 struts: 0.46 -> BATCH_MEASURED ms with the stream below made
+    // anew by each call, 0.2 ms of it): it launches them directly.
+    size_t in_call = 0;
+    LSL_TRY(for_groups(b, k0, nk, [&](int, int, int) -> lsl_status {
+        ++in_call;
+        return LSL_OK;
+    }));
     size_t n_call_groups = 0;
     LSL_TRY(for_groups(b, k0, nk, [&](int g, int s_lo, int s_hi) -> lsl_status {
         if (b->stage_events.size() <= n_call_groups) {
@@ -1643,17 +1742,26 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
         hipEvent_t* ev = b->stage_events[n_call_groups++].ev;
         LSL_HIP(hipEventRecord(ev[0], st));
         LSL_TRY(ensure_group(b, g, st));
+        if (in_call == 1) {
+            LSL_HIP(hipEventRecord(ev[1], st));
+            for (int ph = 0; ph < 3; ++ph) {
+                LSL_TRY(batch_group_work(b, g, k0, nk, s_lo, s_hi, field, bits, segs, capacity,
+                                         offsets, ph, st));
+                LSL_HIP(hipEventRecord(ev[2 + ph], st));
+            }
+            return LSL_OK;
+        }
         // the group's three phases, recorded on the capture stream, then
         // launched through the process's graph cache: the launch shape (what
         // decides which kernels run) and which of the shape's two entries
         // this group takes
-        if (!cap) LSL_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+        if (!b->cap) LSL_HIP(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
         const int32_t planes = slab_planes(b->slab, std::min(k0 + nk, (s_hi + 1) * b->slab) -
                                                         std::max(k0, s_lo * b->slab));
         hipGraph_t gr[3] = {nullptr, nullptr, nullptr};
         lsl_status cs = LSL_OK;
         for (int ph = 0; ph < 3 && cs == LSL_OK; ++ph)
-            cs = capture(cap, &gr[ph], [&](hipStream_t cs_st) {
+            cs = capture(b->cap, &gr[ph], [&](hipStream_t cs_st) {
                 return batch_group_work(b, g, k0, nk, s_lo, s_hi, field, bits, segs, capacity,
                                         offsets, ph, cs_st);
             });
@@ -1673,10 +1781,10 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
             if (x) hipGraphDestroy(x);
         return cs;
     }));
-    if (cap) hipStreamDestroy(cap);
-    unsigned long long tot = 0;
-    LSL_HIP(hipMemcpyAsync(&tot, base, 8, hipMemcpyDeviceToHost, st));
-    LSL_HIP(hipStreamSynchronize(st));
+    HostBuf hb;
+    LSL_TRY(hb.get(8));
+    LSL_HIP(hb.read(base, 8, st));
+    const unsigned long long tot = *(const unsigned long long*)hb.p;
     // stage times of this call from its event sets
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     bool ok = true;

@@ -97,11 +97,15 @@ __device__ __forceinline__ uint32_t cell_count(const SRange& r, int32_t sa, int3
     return (uint32_t)(s1 - s0 + 1) * row_segments(r);
 }
 
-__global__ void k_pair_counts(const uint32_t* active, uint32_t n, const SRange* rg, int32_t sa,
+// ALL: the group starts with the first slab, so that its active struts are the
+// first n of the edge list; the list is written here.
+template <bool ALL>
+__global__ void k_pair_counts(uint32_t* active, uint32_t n, const SRange* rg, int32_t sa,
                               int32_t sb, uint32_t* counts, uint32_t* rcounts) {
     const uint32_t a = blockIdx.x * blockDim.x + threadIdx.x;
     if (a < n) {
-        const SRange r = rg[active[a]];
+        if (ALL) active[a] = a;
+        const SRange r = rg[ALL ? a : active[a]];
         counts[a] = pair_count(r, sa, sb);
         rcounts[a] = cell_count(r, sa, sb);
     }
@@ -224,6 +228,7 @@ __global__ __launch_bounds__(256) void k_cell_buckets(const uint32_t* coffs, con
         }
     }
     if (!FILL && owner) counts[b0 + (size_t)tx_own] = cur;
+    if (!FILL && cell == 0u && lane == 0) counts[(size_t)(n_cells / (uint32_t)nseg) * (size_t)ntx] = 0u;
 }
 
 // offsets[b] = first sorted position whose key is >= b
@@ -278,7 +283,7 @@ int bits_for(uint32_t n) {
 
 size_t group_tmp_elems(size_t n_pairs, size_t n_active, size_t n_cand, size_t n_buckets) {
     size_t a = radix_tmp_elems(n_pairs);
-    size_t b = scan_tmp_elems(n_active + 1);
+    size_t b = 2 * scan_tmp_elems(n_active + 1);
     size_t c = scan_tmp_elems(n_cand / kCTile + 1);
     size_t d = scan_tmp_elems(n_buckets + 1);
     size_t m = a > b ? a : b;
@@ -289,7 +294,8 @@ size_t group_tmp_elems(size_t n_pairs, size_t n_active, size_t n_cand, size_t n_
 lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
     // 1. active list: kept part of the previous list plus the new range
     const size_t n_cand = (size_t)g.n_prev + (g.range_hi - g.range_lo);
-    if (n_cand > 0) {
+    const bool all = g.n_prev == 0 && g.range_lo == 0 && g.sa == 0;
+    if (n_cand > 0 && !all) {
         const size_t nb = (n_cand + kCTile - 1) / kCTile;
         k_active_count<<<(unsigned)nb, kCThreads, 0, st>>>(g.prev_active, g.n_prev, g.range_lo,
                                                            n_cand, g.ranges, g.sa, g.blk);
@@ -301,10 +307,10 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
     }
     // 2. pairs per active strut -> emission offsets (the adjoint's emission
     // index); cells per active strut -> their offsets
-    k_pair_counts<<<(g.n_active + 1 + 255) / 256, 256, 0, st>>>(g.active, g.n_active, g.ranges,
-                                                                g.sa, g.sb, g.eoff, g.toff);
-    LSL_TRY(exclusive_scan_u32(g.eoff, g.eoff, (size_t)g.n_active + 1, g.tmp, nullptr, st));
-    LSL_TRY(exclusive_scan_u32(g.toff, g.toff, (size_t)g.n_active + 1, g.tmp, nullptr, st));
+    (all ? k_pair_counts<true> : k_pair_counts<false>)<<<(g.n_active + 1 + 255) / 256, 256, 0, st>>>(
+        g.active, g.n_active, g.ranges, g.sa, g.sb, g.eoff, g.toff);
+    LSL_HIP(hipGetLastError());
+    LSL_TRY(exclusive_scan_u32(g.eoff, g.eoff, (size_t)g.n_active + 1, g.tmp, nullptr, st, g.toff));
     const uint32_t nseg = (uint32_t)((g.ntx + kSegTiles - 1) / kSegTiles);
     const uint32_t n_cells = (uint32_t)(g.sb - g.sa + 1) * (uint32_t)g.nty * nseg;
     if (g.n_pairs > 0 && g.n_cells > 0) {
@@ -332,7 +338,7 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
         k_cell_buckets<false><<<gr, 256, 0, st>>>(g.roffs, cv, g.ranges, n_cells, g.ntx,
                                                   (int32_t)nseg, g.offsets, nullptr, nullptr, 0u);
         LSL_HIP(hipGetLastError());
-        LSL_TRY(fill_u32(g.offsets + g.n_buckets, 0u, 1, st));
+        // (the count pass also clears the place after the last bucket)
         LSL_TRY(exclusive_scan_u32(g.offsets, g.offsets, (size_t)g.n_buckets + 1, g.tmp, nullptr,
                                    st));
         // 6. the bucket lists, into the buffers not holding the sorted cells

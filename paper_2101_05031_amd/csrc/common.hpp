@@ -125,8 +125,11 @@ const char* last_error();
 // scan_tmp_elems(n) elements of the same type.  Writes the total to
 // *total_dev when non-null.
 size_t scan_tmp_elems(size_t n);
+// also: a second array of n values, scanned in place by the same launches (tmp
+// then holds twice as many elements).
 lsl_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, size_t n,
-                              uint32_t* tmp, uint32_t* total_dev, hipStream_t st);
+                              uint32_t* tmp, uint32_t* total_dev, hipStream_t st,
+                              uint32_t* also = nullptr);
 lsl_status exclusive_scan_u64(const uint64_t* in, uint64_t* out, size_t n,
                               uint64_t* tmp, uint64_t* total_dev, hipStream_t st);
 

@@ -311,9 +311,11 @@ lsl_status loss_t(const DensityArgs& a, const void* field, double C, double tau,
                   hipStream_t st) {
     double* part = scratch;
     const T inv_tau = (T)(1.0 / tau);
-    // the gradient's second pass reads what the first has just read: unused
-    // LDS holds the blocks in flight to four per compute unit
-    constexpr unsigned kPad = 36 * 1024;
+    // the gradient's second pass reads what the first has just read: where
+    // the boxes of all blocks that fit the GPU at once would not stay in the
+    // memory-side cache, unused LDS holds them to four per compute unit
+    const size_t box = (size_t)kDThreads * (size_t)a.vy * (size_t)a.vz * sizeof(T);
+    const unsigned kPad = box > 64 * 1024 ? 36 * 1024 : 0;
     if (grad)
         k_soft_density<T, true><<<a.n_blocks, kDThreads, kPad, st>>>(
             (const T*)field, a, (T)C, inv_tau, tau, target, soft, (T*)grad, part);

@@ -49,7 +49,8 @@ struct GatherArgs {
     const void* nodes;
     const int32_t* edges;
     const void* weight;
-    const uint32_t* perm;             // [n_binned] sorted position -> edge id
+    const uint32_t* perm_src;         // [n_binned] sorted position -> edge id
+    uint32_t* perm;                   // [n_binned] its copy
     const SRange* ranges_by_id;
     const PRange* pranges_by_id;
     int64_t n_binned;

@@ -231,7 +231,8 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_gather(GatherArgs a) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_binned) return;
-    const uint32_t e = a.perm[p];
+    const uint32_t e = a.perm_src[p];
+    a.perm[p] = e;
     const int32_t ia = a.edges[2 * (size_t)e], ib = a.edges[2 * (size_t)e + 1];
     const T* nd = (const T*)a.nodes;
     const double w = (double)((const T*)a.weight)[e];

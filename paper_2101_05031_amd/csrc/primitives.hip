@@ -97,8 +97,13 @@ __device__ __forceinline__ void store_run(T* out, size_t base, size_t n, T pre,
 }
 
 template <typename T>
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const T* in, size_t n, T* sums) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const T* in, size_t n, T* sums,
+                                                              const T* also) {
     __shared__ T sm[4];
+    if (blockIdx.y) {                  // the second array: its totals follow the first's
+        in = also;
+        sums += gridDim.x;
+    }
     const size_t base = (size_t)blockIdx.x * kScanTile + (size_t)threadIdx.x * kScanItems;
     T v[kScanItems];
     const T s = load_run(in, base, n, v);
@@ -110,9 +115,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const T* in, size_
 // Single block: exclusive scan of n values, carry across chunks (in may be
 // out).
 template <typename T>
-__global__ __launch_bounds__(kScanThreads) void k_scan_one(const T* in, T* out, size_t n,
-                                                           T* total) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_one(const T* in, T* out, size_t n, T* total,
+                                                           T* also, size_t also_step) {
     __shared__ T sm[4];
+    if (blockIdx.y) in = out = also ? also : out + also_step;
     T carry = 0;
     for (size_t c = 0; c < n; c += kScanTile) {
         const size_t base = c + (size_t)threadIdx.x * kScanItems;
@@ -131,8 +137,12 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_one(const T* in, T* out, 
 // launch of their own); else they have been scanned.
 template <typename T, bool RAW>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(const T* in, T* out, size_t n,
-                                                            const T* sums, T* total) {
+                                                            const T* sums, T* total, T* also) {
     __shared__ T sm[4];
+    if (blockIdx.y) {
+        in = out = also;
+        sums += gridDim.x;
+    }
     T before;
     if (RAW) {
         T s = 0;
@@ -147,7 +157,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const T* in, T* out,
     T tot;
     const T pre = block_exclusive_scan(s, sm, &tot) + before;
     store_run(out, base, n, pre, v);
-    if (total && threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total = before + tot;
+    if (total && threadIdx.x == 0 && blockIdx.y == 0 && blockIdx.x == gridDim.x - 1)
+        *total = before + tot;
 }
 
 // Up to kScanOne values take one block (its chunks are serial, about 1 us
@@ -158,21 +169,22 @@ constexpr size_t kScanOne = 4 * (size_t)kScanTile;
 constexpr size_t kScanRaw = 4096;
 
 template <typename T>
-lsl_status scan_impl(const T* in, T* out, size_t n, T* tmp, T* total, hipStream_t st) {
+lsl_status scan_impl(const T* in, T* out, size_t n, T* tmp, T* total, hipStream_t st, T* also) {
     const size_t nb = (n + kScanTile - 1) / kScanTile;
+    const unsigned na = also ? 2u : 1u;
     if (n <= kScanOne) {
-        if (n > 0 || total) k_scan_one<T><<<1, kScanThreads, 0, st>>>(in, out, n, total);
+        if (n > 0 || total)
+            k_scan_one<T><<<dim3(1, na), kScanThreads, 0, st>>>(in, out, n, total, also, 0);
         LSL_HIP(hipGetLastError());
         return LSL_OK;
     }
-    k_scan_reduce<T><<<dim3((unsigned)nb), dim3(kScanThreads), 0, st>>>(in, n, tmp);
+    const dim3 grid((unsigned)nb, na);
+    k_scan_reduce<T><<<grid, dim3(kScanThreads), 0, st>>>(in, n, tmp, also);
     if (nb <= kScanRaw) {
-        k_scan_down<T, true><<<dim3((unsigned)nb), dim3(kScanThreads), 0, st>>>(in, out, n, tmp,
-                                                                                total);
+        k_scan_down<T, true><<<grid, dim3(kScanThreads), 0, st>>>(in, out, n, tmp, total, also);
     } else {
-        k_scan_one<T><<<1, kScanThreads, 0, st>>>(tmp, tmp, nb, nullptr);
-        k_scan_down<T, false><<<dim3((unsigned)nb), dim3(kScanThreads), 0, st>>>(in, out, n, tmp,
-                                                                                 total);
+        k_scan_one<T><<<dim3(1, na), kScanThreads, 0, st>>>(tmp, tmp, nb, nullptr, nullptr, nb);
+        k_scan_down<T, false><<<grid, dim3(kScanThreads), 0, st>>>(in, out, n, tmp, total, also);
     }
     LSL_HIP(hipGetLastError());
     return LSL_OK;
@@ -477,13 +489,13 @@ unsigned grid_for(size_t n, unsigned threads) {
 size_t scan_tmp_elems(size_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
 lsl_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, size_t n, uint32_t* tmp,
-                              uint32_t* total, hipStream_t st) {
-    return scan_impl<uint32_t>(in, out, n, tmp, total, st);
+                              uint32_t* total, hipStream_t st, uint32_t* also) {
+    return scan_impl<uint32_t>(in, out, n, tmp, total, st, also);
 }
 
 lsl_status exclusive_scan_u64(const uint64_t* in, uint64_t* out, size_t n, uint64_t* tmp,
                               uint64_t* total, hipStream_t st) {
-    return scan_impl<uint64_t>(in, out, n, tmp, total, st);
+    return scan_impl<uint64_t>(in, out, n, tmp, total, st, nullptr);
 }
 
 size_t radix_tmp_elems(size_t n) {
