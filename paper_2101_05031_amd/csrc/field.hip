@@ -6,9 +6,9 @@
 // coarse against the smallest support (every plane staged from float64).
 //
 // One wave owns an 8x8 pixel block of one tile and one slab of planes.  The
-// wave walks its tile's bucket
-// list (edge-list order) 64 struts at a time.  Per strut and plane it stages,
-// in float64, the foot F of the block centre c on the strut's line:
+// wave walks its tile's bucket list (edge-list order) 64 struts at a time.  Per
+// strut and plane that may reach the block it stages, in float64, the foot F
+// of the block centre c on the strut's line:
 //
 //   tc = (c - a).u,  m = a + tc u - c  (m is orthogonal to u),
 //
@@ -48,8 +48,14 @@ namespace {
 
 // Waves per SIMD the kernels are built for: the registers of one or two
 // planes fit eight (64 each), of four planes six; eight and more planes are
-// fastest with five (96 registers; four and six measured 9% and 3% slower).
-constexpr int field_waves(int SZ) { return SZ <= 2 ? 8 : SZ <= 4 ? 6 : 5; }
+// fastest with five (96 registers; four and six measured 9% and 3% slower),
+// but the float32 kernels of field_block.hpp, which keep less between planes,
+// with six (per-strut supports 1.37 -> 1.33 ms, the Gaussian 2.71 -> 2.59 ms).
+template <typename T>
+constexpr int field_waves(int SZ, int form) {
+    const bool small = sizeof(T) == 4 && form == kFormBlock && SZ <= 8;
+    return SZ <= 2 ? 8 : SZ <= 4 || small ? 6 : 5;
+}
 
 // One wave per workgroup takes one 8x8 block of one (slab, tile) item.  The
 // items come in the order of `queue` (descending cost, slice_batch), the
@@ -64,7 +70,7 @@ constexpr int field_waves(int SZ) { return SZ <= 2 ? 8 : SZ <= 4 ? 6 : 5; }
 // persistent workgroups of four waves 8.0 ms, this 7.7 ms;
 // 812 float64 struts, 50 planes of 256^2: 54 and 36 us.
 template <typename T, int SZ, bool STATS, int K, bool SR, int FORM>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(field_waves(SZ)))) void
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(field_waves<T>(SZ, FORM)))) void
 k_field(FieldArgs a, const uint32_t* queue, uint32_t item0, uint32_t n_items) {
     const int nsub = a.tile / kBlockPix, nsub2 = nsub * nsub;
     const uint32_t xcd = blockIdx.x % 8u, u = blockIdx.x / 8u;
@@ -92,9 +98,9 @@ k_field(FieldArgs a, const uint32_t* queue, uint32_t item0, uint32_t n_items) {
     } else {
         __shared__ Stage<T> stage[kWave];
         __shared__ T pend[fieldk::pend_elems<T, SZ>()];
-        __shared__ double line[fieldk::kLineVals * kWave];
+        __shared__ fieldk::Pairs<SZ> pairs;
         fieldk::field_block<T, SZ, STATS, K, SR>(a, a.s_lo + (int)t, tx, ty, sub, stage, pend,
-                                                 line);
+                                                 pairs);
     }
 }
 
