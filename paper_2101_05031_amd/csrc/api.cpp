@@ -724,6 +724,7 @@ FieldArgs field_args(const lattice_bins* b, int32_t k0, int32_t nk, void* field)
     a.C = b->C;
     a.field = field;
     a.bits_blk = nullptr;
+    a.bits_rows = nullptr;
     return a;
 }
 
@@ -1253,21 +1254,17 @@ lsl_status slice_field(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
             LSL_TRY(fill_bytes0(bits, (size_t)nk * b->grid.H * ((b->grid.W + 31) / 32) * 4, st));
         return LSL_OK;
     }
-    // binary images: block-major in library scratch, then the caller's
-    // row-major copy
-    if (bits) LSL_TRY(ensure_cbits(b, nk, st));
     // the plan covers every slab, so every block of every plane is written
     LSL_TRY(for_groups(b, k0, nk, [&](int g, int s_lo, int s_hi) -> lsl_status {
         LSL_TRY(ensure_group(b, g, st));
         FieldArgs a = field_args(b, k0, nk, field);
-        a.bits_blk = bits ? (uint64_t*)b->cbits : nullptr;
+        a.bits_rows = (uint8_t*)bits;
         a.n_pairs = (uint32_t)b->groups[g].pairs;
         a.group_s0 = b->groups[g].sa;
         a.s_lo = s_lo;
         a.s_hi = s_hi;
         return launch_field(b->dtype, a, false, nullptr, st);
     }));
-    if (bits) LSL_TRY(launch_bits_rows((const uint64_t*)b->cbits, nk, b->grid.W, b->grid.H, bits, st));
     return LSL_OK;
 }
 
@@ -1448,29 +1445,36 @@ lsl_status slice_density_loss(const lattice_bins* cb, int32_t nk, const void* fi
 
 namespace {
 
-// Node -> (strut, end) incidence list in edge-list order, built once.
+// Node -> (strut, end) incidence list in edge-list order, built once.  The
+// struts' ends are the sort's keys; its scratch is the adjoint's partial sums,
+// which nothing holds yet, where they are large enough (a new handle's first
+// adjoint then neither allocates nor waits for it).
 lsl_status ensure_node_csr(lattice_bins* b, hipStream_t st) {
     if (b->node_off) return LSL_OK;
-    const size_t n2 = 2 * (size_t)std::max<uint32_t>(b->n_binned, 1);
-    uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr, *tmp = nullptr;
-    lsl_status s;
-    if ((s = b->alloc_t(&k0, n2)) || (s = b->alloc_t(&v0, n2)) || (s = b->alloc_t(&k1, n2)) ||
-        (s = b->alloc_t(&v1, n2)) || (s = b->alloc_t(&tmp, radix_tmp_elems(n2))) ||
-        (s = b->alloc_t(&b->node_off, (size_t)b->n_nodes + 1)) ||
-        (s = b->alloc_t(&b->node_inc, n2)))
-        return s;
-    const size_t n = 2 * (size_t)b->n_binned;
-    LSL_TRY(launch_node_keys(b->ends, b->n_binned, k0, v0, st));
-    int bits = 0;
+    const size_t n = 2 * (size_t)b->n_binned, n2 = std::max<size_t>(n, 2);
+    uint32_t *off = nullptr, *inc = nullptr, *scratch = nullptr;
+    LSL_TRY(b->alloc_t(&off, (size_t)b->n_nodes + 1));
+    LSL_TRY(b->alloc_t(&inc, n2));
+    const size_t need = 3 * n2 + radix_tmp_elems(n2);
+    const bool own = need * 4 > b->cap_pairs * 9 * b->esize();
+    if (own)
+        LSL_TRY(b->alloc_t(&scratch, need));
+    else
+        scratch = (uint32_t*)b->partial;
+    int bits = 1;
     while (bits < 32 && (1ull << bits) < (uint64_t)b->n_nodes) ++bits;
-    int which = 0;
-    LSL_TRY(radix_sort_pairs(k0, v0, k1, v1, n, bits, tmp, &which, st));
-    const uint32_t* ks = which ? k1 : k0;
-    const uint32_t* vs = which ? v1 : v0;
-    LSL_TRY(launch_node_offsets(ks, n, b->n_nodes, b->node_off, st));
-    if (n) LSL_HIP(hipMemcpyAsync(b->node_inc, vs, n * 4, hipMemcpyDeviceToDevice, st));
-    LSL_HIP(hipStreamSynchronize(st));
-    for (void* p : {(void*)k0, (void*)v0, (void*)k1, (void*)v1, (void*)tmp}) b->release(p);
+    // the last pass writes the list
+    uint32_t *k0 = scratch, *k1 = k0 + n2, *v = k1 + n2, *tmp = v + n2;
+    const bool odd = radix_passes(n, bits) & 1;
+    LSL_TRY(radix_sort_places((const uint32_t*)b->ends, k0, odd ? inc : v, k1, odd ? v : inc, n,
+                              bits, tmp, st));
+    LSL_TRY(launch_node_offsets(odd ? k0 : k1, n, b->n_nodes, off, st));
+    if (own) {
+        LSL_HIP(hipStreamSynchronize(st));
+        b->release(scratch);
+    }
+    b->node_off = off;
+    b->node_inc = inc;
     return LSL_OK;
 }
 

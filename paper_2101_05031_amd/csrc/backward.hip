@@ -1176,16 +1176,6 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs a, const SRange* rang
     }
 }
 
-__global__ void k_node_keys(const int2* ends, int64_t n, uint32_t* keys, uint32_t* vals) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    const int2 e = ends[p];
-    keys[2 * p] = (uint32_t)e.x;
-    vals[2 * p] = (uint32_t)(2 * p);
-    keys[2 * p + 1] = (uint32_t)e.y;
-    vals[2 * p + 1] = (uint32_t)(2 * p + 1);
-}
-
 __global__ void k_node_offsets(const uint32_t* keys, uint32_t n, uint32_t n_nodes,
                                uint32_t* off) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1271,14 +1261,6 @@ lsl_status launch_reduce(int dtype, const ReduceArgs& a, const SRange* ranges, i
         k_reduce<float><<<g, 256, 0, st>>>(a, ranges, sa, s_lo, s_hi, n_pairs, n_binned);
     else
         k_reduce<double><<<g, 256, 0, st>>>(a, ranges, sa, s_lo, s_hi, n_pairs, n_binned);
-    LSL_HIP(hipGetLastError());
-    return LSL_OK;
-}
-
-lsl_status launch_node_keys(const int2* ends, int64_t n_binned, uint32_t* keys, uint32_t* vals,
-                            hipStream_t st) {
-    if (n_binned == 0) return LSL_OK;
-    k_node_keys<<<(unsigned)((n_binned + 255) / 256), 256, 0, st>>>(ends, n_binned, keys, vals);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }

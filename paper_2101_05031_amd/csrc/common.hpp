@@ -146,6 +146,13 @@ lsl_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* 
                             size_t n, int key_bits, uint32_t* tmp, int* which,
                             hipStream_t st, const uint32_t* n_keep = nullptr);
 
+// The same sort of (keys[i], i): `keys` is only read.  The result is in
+// (k0, v0) after an odd number of passes (radix_passes), else in (k1, v1).
+int radix_passes(size_t n, int key_bits);
+lsl_status radix_sort_places(const uint32_t* keys, uint32_t* k0, uint32_t* v0, uint32_t* k1,
+                             uint32_t* v1, size_t n, int key_bits, uint32_t* tmp,
+                             hipStream_t st);
+
 lsl_status fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 lsl_status fill_bytes0(void* p, size_t bytes, hipStream_t st);
 lsl_status iota_u32(uint32_t* p, uint32_t base, size_t n, hipStream_t st);

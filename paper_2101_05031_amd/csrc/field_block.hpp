@@ -442,19 +442,22 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
                 out[((size_t)(kb + k - a.k0) * (size_t)a.H + (size_t)pj) * (size_t)a.W + (size_t)pi] =
                     acc_s[k] + acc_c[k];
     }
-    if (a.bits_blk) {
-        // binary image, block-major: the block's ballot is its word
-        const size_t nbx = (size_t)(a.W + 7) / 8, nby = (size_t)(a.H + 7) / 8;
+    if (a.bits_blk || a.bits_rows) {
+        // binary image: the block's ballot
         const T C = (T)a.C;
 #pragma unroll
         for (int k = 0; k < SZ; ++k) {
-            if (k < nvalid) {
-                const uint64_t m = ballot64(pix && acc_s[k] + acc_c[k] >= C);
-                if (lane == 0)
-                    a.bits_blk[((size_t)(kb + k - a.k0) * nby + (size_t)(j0 >> 3)) * nbx +
-                               (size_t)(i0 >> 3)] = m;
+            const uint64_t m = ballot64(pix && acc_s[k] + acc_c[k] >= C);
+            if (lane == k) {                       // (through LDS: one copy of the stores' code)
+                pl.id[2 * k] = (uint32_t)m;
+                pl.id[2 * k + 1] = (uint32_t)(m >> 32);
             }
         }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int k = 0; k < nvalid; ++k)
+            store_bits(a, kb + k - a.k0, i0, j0,
+                       (uint64_t)pl.id[2 * k] | ((uint64_t)pl.id[2 * k + 1] << 32), lane);
     }
 }
 

@@ -469,19 +469,22 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
                     __builtin_ldexpf(S.acc_s[k] + S.acc_c[k], 5 * a.wexp);
         });
     }
-    if (a.bits_blk) {
-        const size_t nbx = (size_t)(a.W + 7) / 8, nby = (size_t)(a.H + 7) / 8;
+    if (a.bits_blk || a.bits_rows) {
         const float C = (float)a.C;
         for_planes<0, SZ>([&](auto kc) {
             constexpr int k = decltype(kc)::value;
-            if (k >= kfirst && k < nvalid) {
-                const uint64_t m =
-                    ballot64(pix && __builtin_ldexpf(S.acc_s[k] + S.acc_c[k], 5 * a.wexp) >= C);
-                if (lane == 0)
-                    a.bits_blk[((size_t)(kb + k - a.k0) * nby + (size_t)(j0 >> 3)) * nbx +
-                               (size_t)(i0 >> 3)] = m;
+            const uint64_t m =
+                ballot64(pix && __builtin_ldexpf(S.acc_s[k] + S.acc_c[k], 5 * a.wexp) >= C);
+            if (lane == k) {                       // (through LDS: one copy of the stores' code)
+                L.queue[2 * k] = (uint32_t)m;
+                L.queue[2 * k + 1] = (uint32_t)(m >> 32);
             }
         });
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int k = kfirst; k < nvalid; ++k)
+            store_bits(a, kb + k - a.k0, i0, j0,
+                       (uint64_t)L.queue[2 * k] | ((uint64_t)L.queue[2 * k + 1] << 32), lane);
     }
 }
 

@@ -149,9 +149,29 @@ struct FieldArgs {
     void* field;                      // [nk][H][W] or null (not written)
     uint64_t* bits_blk;               // [nk][ceil(H/8)][ceil(W/8)] or null: field >= C,
                                       // one word per 8x8 block (bit 8*row+col)
+    uint8_t* bits_rows;               // [nk][H][4 ceil(W/32)] bytes or null: the same row by row
+                                      // (bit x % 8 of byte x / 8)
     double C;
     unsigned long long* stats;        // [3] (stats kernels only)
 };
+
+// A wave's 8x8 block (i0, j0) of the binary image of plane k (from k0 on):
+// m, bit 8 row + column.  Row by row each of eight lanes writes its byte, and
+// the last block of a row clears the rest of the row's last word; a block-major
+// image and a pass to transpose it cost one plane of 2048^2 6 us more.
+__device__ __forceinline__ void store_bits(const FieldArgs& a, int k, int i0, int j0, uint64_t m,
+                                           int lane) {
+    if (a.bits_blk && lane == 0)
+        a.bits_blk[((size_t)k * (size_t)((a.H + 7) / 8) + (size_t)(j0 >> 3)) *
+                       (size_t)((a.W + 7) / 8) + (size_t)(i0 >> 3)] = m;
+    if (a.bits_rows && lane < 8 && j0 + lane < a.H) {
+        const int bytes = 4 * ((a.W + 31) / 32);
+        uint8_t* row = a.bits_rows + ((size_t)k * (size_t)a.H + (size_t)(j0 + lane)) * (size_t)bytes;
+        row[i0 >> 3] = (uint8_t)(m >> (8 * lane));
+        if (i0 + 8 >= a.W)
+            for (int b = (i0 >> 3) + 1; b < bytes; ++b) row[b] = 0;
+    }
+}
 // The planes per slab that the field kernels are built for: the power of two
 // that holds the planes a call evaluates in any slab.  A call for fewer
 // planes than a slab holds takes the smaller kernel (the field does not
@@ -254,8 +274,6 @@ struct ScatterArgs {
     int32_t accumulate;
 };
 lsl_status launch_scatter(int dtype, const ScatterArgs& a, hipStream_t st);
-lsl_status launch_node_keys(const int2* ends, int64_t n_binned, uint32_t* keys,
-                            uint32_t* vals, hipStream_t st);
 lsl_status launch_node_offsets(const uint32_t* sorted_keys, size_t n, int64_t n_nodes,
                                uint32_t* node_off, hipStream_t st);
 

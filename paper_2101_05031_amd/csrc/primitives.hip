@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kOneThreads) void k_radix_one(const uint32_t* kin,
     for (int r = 0; r < kSortItems; ++r) {
         const uint32_t i = i0 + (uint32_t)r * kWave;
         k[r] = r < rounds && i < n ? kin[i] : 0u;
-        v[r] = r < rounds && i < n ? vin[i] : 0u;
+        v[r] = !vin ? i : r < rounds && i < n ? vin[i] : 0u;
     }
     for (int shift = 0; shift < key_bits; shift += 8) {
         for (int i = t; i < kOneWaves * 256; i += kOneThreads) (&cnt[0][0])[i] = 0u;
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     for (int r = 0; r < kSortItems; ++r) {
         const size_t i = i0 + (size_t)r * kWave;
         k[r] = i < n ? kin[i] : 0u;
-        v[r] = i < n ? vin[i] : 0u;
+        v[r] = !vin ? (uint32_t)i : i < n ? vin[i] : 0u;       // (no values: the places)
     }
     // digit t: items of all blocks, and of the blocks before this one
     uint32_t all = 0, before = 0;
@@ -514,6 +514,41 @@ void radix_pass(const uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* 
                                                             dtot, nb);
 }
 }  // namespace
+
+int radix_passes(size_t n, int key_bits) {
+    return n <= kSortOne ? 1 : (key_bits + 7) / 8;
+}
+
+lsl_status radix_sort_places(const uint32_t* keys, uint32_t* k0, uint32_t* v0, uint32_t* k1,
+                             uint32_t* v1, size_t n, int key_bits, uint32_t* tmp,
+                             hipStream_t st) {
+    if (n == 0) return LSL_OK;
+    if (key_bits < 1) key_bits = 1;
+    const uint32_t *ki = keys, *vi = nullptr;
+    if (n <= kSortOne) {
+        k_radix_one<<<1, kOneThreads, 0, st>>>(ki, vi, k0, v0, (uint32_t)n, key_bits);
+        LSL_HIP(hipGetLastError());
+        return LSL_OK;
+    }
+    const size_t nb = (n + kSortTile - 1) / kSortTile;
+    if (n > 0xffffffffull) {
+        set_error("radix sort: too many items");
+        return LSL_EINTERNAL;
+    }
+    uint32_t *ko = k0, *vo = v0, *kn = k1, *vn = v1;
+    for (int shift = 0; shift < key_bits; shift += 8) {
+        (nb <= kSortRaw ? radix_pass<true, false> : radix_pass<false, false>)(
+            ki, vi, ko, vo, n, nullptr, shift, tmp, (uint32_t)nb, st);
+        LSL_HIP(hipGetLastError());
+        ki = ko;
+        vi = vo;
+        ko = kn;
+        vo = vn;
+        kn = (uint32_t*)ki;
+        vn = (uint32_t*)vi;
+    }
+    return LSL_OK;
+}
 
 lsl_status radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, size_t n,
                             int key_bits, uint32_t* tmp, int* which, hipStream_t st,

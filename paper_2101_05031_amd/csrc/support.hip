@@ -149,15 +149,6 @@ __global__ void k_support_edge_grad(const T* nodes, const int32_t* edges, const 
     te[3 * j + 2] = gz;
 }
 
-__global__ void k_inc_keys(const int32_t* edges, int64_t n_edges, uint32_t* keys, uint32_t* vals) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n_edges) return;
-    keys[2 * j] = (uint32_t)edges[2 * j];            // v_s
-    vals[2 * j] = (uint32_t)(2 * j);
-    keys[2 * j + 1] = (uint32_t)edges[2 * j + 1];    // v_e
-    vals[2 * j + 1] = (uint32_t)(2 * j + 1);
-}
-
 // off[n] = first sorted position whose node is >= n
 __global__ void k_inc_offsets(const uint32_t* keys, uint32_t n, uint32_t n_nodes, uint32_t* off) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -198,18 +189,19 @@ lsl_status support_t(const SupportArgs& a, hipStream_t st) {
     LSL_HIP(hipGetLastError());
     if (!a.grad) return LSL_OK;
     const unsigned g = (unsigned)((a.n_edges + 255) / 256);
-    if (a.n_edges > 0) {
+    if (a.n_edges > 0)
         k_support_edge_grad<T><<<g, 256, 0, st>>>(nodes, a.edges, weight, a.n_nodes, a.n_edges,
                                                   a.t[0], a.t[1], a.t[2], a.sums, a.te, a.err);
-        k_inc_keys<<<g, 256, 0, st>>>(a.edges, a.n_edges, a.k0, a.v0);
-    }
+    // incidences by node: the edge array is the keys, 2 j and 2 j + 1 the ends
+    // v_s and v_e of edge j
     const size_t n2 = 2 * (size_t)a.n_edges;
-    int which = 0;
-    int bits = 0;
+    int bits = 1;
     while (bits < 32 && (1ull << bits) < (uint64_t)a.n_nodes) ++bits;
-    LSL_TRY(radix_sort_pairs(a.k0, a.v0, a.k1, a.v1, n2, bits, a.tmp, &which, st));
-    const uint32_t* ks = which ? a.k1 : a.k0;
-    const uint32_t* vs = which ? a.v1 : a.v0;
+    LSL_TRY(radix_sort_places((const uint32_t*)a.edges, a.k0, a.v0, a.k1, a.v1, n2, bits, a.tmp,
+                              st));
+    const bool odd = radix_passes(n2, bits) & 1;
+    const uint32_t* ks = odd ? a.k0 : a.k1;
+    const uint32_t* vs = odd ? a.v0 : a.v1;
     k_inc_offsets<<<(unsigned)((n2 + 1 + 255) / 256), 256, 0, st>>>(ks, (uint32_t)n2,
                                                                      (uint32_t)a.n_nodes, a.off);
     k_support_gather<T><<<(unsigned)((a.n_nodes + 255) / 256), 256, 0, st>>>(
