@@ -183,16 +183,18 @@ lsl_status lattice_bin(const lsl_lattice* lattice, const lsl_grid* grid,
 lsl_status lattice_bins_free(lattice_bins* bins);
 
 /* Returns every cached device buffer to the device (hipFree, after
- * synchronising each device that holds some) and releases the cached
- * executable graphs of slice_batch (after their last launches complete).
+ * synchronising each device that holds some), releases the cached executable
+ * graphs of slice_batch (after their last launches complete) and frees the
+ * page-locked read-back buffers that are kept (at most eight of 64 KB).
  * *cached_bytes (host, nullable) receives the bytes the buffer cache held.
  * Setting LSL_NO_CACHE=1 in the environment before the first call disables
  * the buffer cache: buffers are then allocated and freed directly. */
 lsl_status lsl_cache_trim(int64_t* cached_bytes);
 
-/* slice_batch runs each slab group as three HIP graphs (work queue, field,
- * image + contours) through one cache of executable graphs per process,
- * shared by every handle: a call records its launches and updates a cached
+/* slice_batch over several slab groups runs each group as three HIP graphs
+ * (work queue, field, image + contours) through one cache of executable graphs
+ * per process, shared by every handle (a call that meets one group launches
+ * its kernels directly): a call records its launches and updates a cached
  * executable graph of the same launch shape (Sec. 6.4: layers differ only
  * in how much work they carry), instantiating one only for a new shape or
  * a refused update.  Two entries per shape serve consecutive groups in
@@ -399,7 +401,8 @@ lsl_status slice_field_backward(lattice_bins* bins, int32_t k0, int32_t nk,
  * slicing time follows the number of struts meeting a plane).  Each group's
  * launches run as three HIP graphs through the process's graph cache (see
  * lsl_graph_cache_stats): recorded per call, instantiated once per launch
- * shape and updated in place afterwards.
+ * shape and updated in place afterwards; a call that meets one group launches
+ * them directly.
  *
  * field: optional [nk][H][W]; when NULL the field is not written (the
  * binary image is built in library scratch, one slab group at a time).

@@ -1,7 +1,7 @@
 """MI355X (gfx950) slicer for convolution-surface lattice structures.
 
 The slicing path (binning, field, binary image, contours, adjoint, batched
-persistent slicing) runs in the native library liblsl.so behind the C ABI of
+slicing) runs in the native library liblsl.so behind the C ABI of
 include/lsl.h; this package only binds it.  Importing the package does not
 load the library; the first call does, and fails if it was not built.
 """

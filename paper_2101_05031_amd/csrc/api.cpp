@@ -1543,6 +1543,7 @@ lsl_status build_queue(lattice_bins* b, const FieldArgs& a, const uint32_t** que
 struct GraphShape {
     int32_t dtype, kernel, gauss_short, strut_R, plane_ref, slab, planes, tile, phase;
     int32_t field, bits, segs, slot;
+    int32_t sort, launches, scan;      // which launches the phases make
 };
 
 // Enqueues one phase of a group's part of slice_batch on `st`:
@@ -1760,8 +1761,10 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
         // decides which kernels run) and which of the shape's two entries
         // this group takes
         if (!b->cap) LSL_HIP(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
-        const int32_t planes = slab_planes(b->slab, std::min(k0 + nk, (s_hi + 1) * b->slab) -
-                                                        std::max(k0, s_lo * b->slab));
+        const int32_t nkg =
+            std::min(k0 + nk, (s_hi + 1) * b->slab) - std::max(k0, s_lo * b->slab);
+        const int32_t planes = slab_planes(b->slab, nkg);
+        const size_t n_items = (size_t)(s_hi - s_lo + 1) * (size_t)b->ntx * (size_t)b->nty;
         hipGraph_t gr[3] = {nullptr, nullptr, nullptr};
         lsl_status cs = LSL_OK;
         for (int ph = 0; ph < 3 && cs == LSL_OK; ++ph)
@@ -1775,7 +1778,10 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
             GraphShape shape{b->dtype, b->kernel, b->gauss_short ? 1 : 0, b->strut_R ? 1 : 0,
                              b->plane_ref ? 1 : 0, b->slab, planes, b->tile, ph,
                              field ? 1 : 0, bits ? 1 : 0, capacity > 0 ? 1 : 0,
-                             (int32_t)((n_call_groups - 1) & 1)};
+                             (int32_t)((n_call_groups - 1) & 1),
+                             radix_form(n_items),
+                             (int32_t)field_launches(b->tile, n_items),
+                             scan_form((size_t)nkg * (size_t)((b->grid.H + 7) / 8) + 1)};
             std::vector<unsigned char> key((unsigned char*)&shape,
                                            (unsigned char*)&shape + sizeof(shape));
             cs = GraphCache::get().launch(key, gr[ph], st);

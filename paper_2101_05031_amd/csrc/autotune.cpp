@@ -1,6 +1,6 @@
 // slice_autotune: picks the tile edge and slab depth for a lattice and grid
 // by binning with each candidate (all slab groups, as one pass over the planes
-// bins them) and timing the persistent field launch of slice_batch on a few
+// bins them) and timing the field launch of slice_batch on a few
 // sampled plane windows.  The field does not depend on the choice (every pixel sees the
 // same struts in the same order), so only speed is compared.  Results are
 // cached in a small JSON file keyed by the problem's shape.
@@ -97,7 +97,7 @@ extern "C" lsl_status slice_autotune(const lsl_lattice* L, const lsl_grid* G,
     }
     std::vector<int> tiles = P->tile ? std::vector<int>{P->tile} : std::vector<int>{16, 32};
     std::vector<int> slabs = P->slab ? std::vector<int>{P->slab} : std::vector<int>{4, 8, 16};
-    // windows of 64 planes: long enough that the persistent launch's tail
+    // windows of 64 planes: long enough that the launch's tail
     // (its last, unevenly sized work items) weighs on every tile as it does
     // on a full pass, which a short window overstates for large tiles
     const int win = std::min(64, G->n_slices);
@@ -157,7 +157,7 @@ extern "C" lsl_status slice_autotune(const lsl_lattice* L, const lsl_grid* G,
             double field_s = 0;
             for (int k0 : starts) {
                 float best_ms = 1e30f;
-                // the persistent path a full pass takes (its field launch,
+                // the batched path a full pass takes (its field launch,
                 // HIP events inside slice_batch); no segments are stored
                 for (int rep = 0; rep < 2; ++rep) {
                     int64_t total = 0;

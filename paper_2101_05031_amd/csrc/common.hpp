@@ -133,6 +133,11 @@ lsl_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, size_t n,
 lsl_status exclusive_scan_u64(const uint64_t* in, uint64_t* out, size_t n,
                               uint64_t* tmp, uint64_t* total_dev, hipStream_t st);
 
+// Which launches a scan or sort of n items makes (graphs of one form differ in
+// their arguments only).
+int scan_form(size_t n);
+int radix_form(size_t n);
+
 // Stable LSD radix sort of (key, value) pairs on key bits [0, key_bits).
 // Input in (k0, v0); (k1, v1) are equal-sized alternates.  Returns in *which
 // 0 if the result is in (k0, v0), 1 if in (k1, v1).  tmp must hold

@@ -144,11 +144,16 @@ __global__ __launch_bounds__(256) void k_bits_blk(const T* field, int32_t nk, in
 // bits); larger calls take several.
 constexpr uint32_t kMaxGroups = 1u << 25;
 
+uint32_t items_per_launch(int32_t tile) {
+    const uint32_t nsub = (uint32_t)(tile / kBlockPix);
+    return kMaxGroups / (nsub * nsub) / 8u * 8u;
+}
+
 template <typename T, int SZ, int K, bool SR, int FORM>
 lsl_status launch_form(const FieldArgs& a, bool stats, const uint32_t* queue, uint32_t n_items,
                        hipStream_t st) {
     const uint32_t nsub2 = (uint32_t)(a.tile / kBlockPix) * (uint32_t)(a.tile / kBlockPix);
-    const uint32_t per_launch = kMaxGroups / nsub2 / 8u * 8u;
+    const uint32_t per_launch = items_per_launch(a.tile);
     for (uint32_t i0 = 0; i0 < n_items; i0 += per_launch) {
         const uint32_t n = n_items - i0 < per_launch ? n_items - i0 : per_launch;
         const uint32_t blocks = (n + 7u) / 8u * 8u * nsub2;
@@ -215,6 +220,10 @@ lsl_status launch_field(int dtype, const FieldArgs& a, bool stats, const uint32_
     }
     return dtype == LSL_F32 ? launch_dt<float>(a, stats, queue, (uint32_t)n_items, st)
                             : launch_dt<double>(a, stats, queue, (uint32_t)n_items, st);
+}
+
+uint32_t field_launches(int32_t tile, uint64_t n_items) {
+    return (uint32_t)((n_items + items_per_launch(tile) - 1) / items_per_launch(tile));
 }
 
 lsl_status launch_bits_blk(int dtype, const void* field, int32_t nk, int32_t W, int32_t H,

@@ -195,6 +195,8 @@ inline int field_form(const FieldArgs& a, int SZ) {
 // or null.
 lsl_status launch_field(int dtype, const FieldArgs& a, bool stats, const uint32_t* queue,
                         hipStream_t st);
+// launches it makes
+uint32_t field_launches(int32_t tile, uint64_t n_items);
 // Block-major binary image (see FieldArgs::bits_blk) of a field.
 lsl_status launch_bits_blk(int dtype, const void* field, int32_t nk, int32_t W, int32_t H,
                            double C, uint64_t* bits_blk, hipStream_t st);

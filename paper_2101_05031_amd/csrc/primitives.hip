@@ -486,6 +486,16 @@ unsigned grid_for(size_t n, unsigned threads) {
 
 }  // namespace
 
+int scan_form(size_t n) {
+    const size_t nb = (n + kScanTile - 1) / kScanTile;
+    return n <= kScanOne ? 0 : nb <= kScanRaw ? 1 : 2;
+}
+
+int radix_form(size_t n) {
+    const size_t nb = (n + kSortTile - 1) / kSortTile;
+    return n <= 1 ? 0 : n <= kSortOne ? 1 : nb <= kSortRaw ? 2 : 3;
+}
+
 size_t scan_tmp_elems(size_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
 lsl_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, size_t n, uint32_t* tmp,

@@ -205,3 +205,31 @@ def test_full_size_batched_sampled(name, k0, nk):
     mine = OC.segments(img[k])
     got = segs[offs[k]:offs[k + 1]].cpu().numpy().astype(np.float64)
     assert np.array_equal(got, mine)
+
+
+def test_graphs_reused_when_groups_launch_differently():
+    """Slab groups of one call whose work queues are sorted by different
+    kernels (up to 8192 items, and more) keep entries of their own: a second
+    call instantiates nothing and gives the plain path's field."""
+    lat, grid = uneven_case()
+    grid.W, grid.H, grid.n_slices = 515, 509, 13
+    probe = bin_lattice(lat, grid, tile=8, slab=1)
+    per_slab = probe.info()["tiles_x"] * probe.info()["tiles_y"]
+    ref = api.slice_field(probe, 0, grid.n_slices)
+    pairs = probe.info()["total_pairs"]
+    sizes = set()
+    for mp in (pairs // 3, pairs // 4, pairs // 5, pairs // 6):
+        b = bin_lattice(lat, grid, tile=8, slab=1, max_pairs=max(mp, 1))
+        n = b.info()["n_groups"]
+        if n < 2:
+            continue
+        sizes |= {(b.group(g)[1] - b.group(g)[0] + 1) * per_slab <= 8192 for g in range(n)}
+        before = None
+        for _ in range(3):
+            field = torch.empty_like(ref)
+            st, total, _, offs = api.slice_batch(b, 0, grid.n_slices, field=field, capacity=0)
+            assert torch.equal(field.view(torch.int32), ref.view(torch.int32))
+            now = api.graph_cache_stats()["instantiated"]
+            assert before is None or now == before
+            before = now
+    assert sizes == {True, False}
