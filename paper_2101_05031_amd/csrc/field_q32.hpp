@@ -303,9 +303,11 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
     // R (1 + 1e-5) + hf of the segment, hf the block's half-diagonal, and that
     // centre lies within hz of the one halfway up the slab's planes: an entry
     // whose segment is R (1 + 1e-4) + hf + hz away from there has an empty reach
-    // mask and is left out (the candidates and their order stay the same).  A
-    // bucket of one chunk is staged as it is.  96 planes of 2048^2 of 1M struts
-    // (164 entries per bucket): 7.7 -> 7.2 ms.
+    // mask and is left out (the candidates and their order stay the same; the
+    // float32 rounding of a place along the strut, 2^-24 of its length, is
+    // added, so that this holds for struts thousands of R long too).  A bucket
+    // of one chunk is staged as it is.  96 planes of 2048^2 of 1M struts (164
+    // entries per bucket): 7.7 -> 7.2 ms.
     const bool filter = end - beg > (uint32_t)kWave;
     const int k_mid2 = 2 * kb + kfirst + nvalid - 1;            // planes kb + kfirst .. kb + nvalid - 1
     const double czm = uniform(a.z0 + 0.5 * (double)(k_mid2 + 1) * a.dz);
@@ -327,7 +329,7 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
                 const double t = fma(wx, ln.x, fma(wy, ln.y, wz * ln.z));
                 const double tt = fmin(fmax(t, 0.0), ln.w);
                 const double ex = fma(-tt, ln.x, wx), ey = fma(-tt, ln.y, wy), ez = fma(-tt, ln.z, wz);
-                const double thr = fma(SR ? (double)r.pad : a.R, 1.0 + 1e-4, hd);
+                const double thr = fma(ln.w, 1e-6, fma(SR ? (double)r.pad : a.R, 1.0 + 1e-4, hd));
                 in = in && !(fma(ex, ex, fma(ey, ey, ez * ez)) >= thr * thr);
             }
             const uint64_t m = ballot64(in);
