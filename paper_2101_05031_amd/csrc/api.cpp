@@ -435,7 +435,7 @@ struct lattice_bins {
     int64_t dev_bytes = 0, peak_bytes = 0;
 
     // per slab group of a slice_batch call, on the caller's stream: before and
-    // after binning the group, after each of the three graphs
+    // after binning the group, after each of the three phases
     struct StageEvents {
         hipEvent_t ev[5];
     };
