@@ -552,13 +552,17 @@ struct Lds<SZ, true, CH> : Spare<SZ >= 4 ? 0 : kRaw + 1, CH> {
 // MODE 0: 16x16 regions, shared reference planes; 1: 16x16 regions, every
 // plane its own reference; 2: 8x8 regions, every plane its own reference
 // and H^ = 1 - |q_perp^|^2 formed from q_perp itself (coarse pixels against
-// the support: the pieces of H^ above would be large).  Every plane its own
-// reference with 8-plane windows holds 16.6 KB of LDS per wave, so at most 9
-// waves fit a compute unit: that mode asks for three waves per SIMD (up to
-// 168 registers) rather than four, which it could not reach.
+// the support: the pieces of H^ above would be large).  Mode 1 takes windows
+// of at most 4 planes: with 8 its per-plane values bring a wave to 16.6 KB of
+// LDS, so that at most 9 waves fit a compute unit (11.5 KB and 13 waves with
+// 4), and a deep window's region pre-test passes nearly every pair.  64 planes
+// of 1024^2 of 115k struts 1.6 mm apart: 0.79 -> 0.63 ms; 32 planes 0.1 mm
+// apart, 1M struts: 2.11 -> 2.00 ms.  Mode 0, whose planes share their values,
+// is slower with 4 (4.45 -> 4.88 ms: twice the wave sums), and so is mode 2
+// (0.53 -> 0.60 ms).
 template <int SZ, bool SR, int MODE>
 __global__ __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(MODE == 1 && SZ == 8 ? 3 : 4))) void k_backward32(
+__attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
     BackArgs a, uint32_t n_items) {
     constexpr int NS = MODE == 2 ? 1 : 2;     // sub-blocks per region side
     constexpr bool PR = MODE != 0;            // per-plane values in LDS
@@ -1071,7 +1075,7 @@ void launch_sz(const BackArgs& a, uint32_t n_items, hipStream_t st) {
     if (!a.wide)
         k_backward32<SZ, SR, 2><<<n_items, 64, 0, st>>>(a, n_items);
     else if (a.plane_ref)
-        k_backward32<SZ, SR, 1><<<n_items, 64, 0, st>>>(a, n_items);
+        k_backward32<SZ >= 8 ? 4 : SZ, SR, 1><<<n_items, 64, 0, st>>>(a, n_items);
     else
         k_backward32<SZ, SR, 0><<<n_items, 64, 0, st>>>(a, n_items);
 }
@@ -1092,7 +1096,7 @@ lsl_status launch(const BackArgs& a, uint32_t n_items, hipStream_t st) {
     else if (a.slab <= 4)
         launch_sr<4>(a, n_items, st);
     else
-        launch_sr<8>(a, n_items, st);      // longer slabs: windows of 8 planes
+        launch_sr<8>(a, n_items, st);      // longer slabs: windows of 8 planes (mode 1: 4)
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }
