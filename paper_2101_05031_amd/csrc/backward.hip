@@ -555,9 +555,9 @@ struct Lds<SZ, true, CH> : Spare<SZ >= 4 ? 0 : kRaw + 1, CH> {
 // the support: the pieces of H^ above would be large).  Mode 1 takes windows
 // of at most 4 planes: with 8 its per-plane values bring a wave to 16.6 KB of
 // LDS, so that at most 9 waves fit a compute unit (11.5 KB and 13 waves with
-// 4), and a deep window's region pre-test passes nearly every pair.  64 planes
-// of 1024^2 of 115k struts 1.6 mm apart: 0.79 -> 0.63 ms; 32 planes 0.1 mm
-// apart, 1M struts: 2.11 -> 2.00 ms.  Mode 0, whose planes share their values,
+// 4), and a deep window's region pre-test passes nearly every pair.  Field, loss
+// and adjoint of 64 planes of 1024^2 of 115k struts 1.6 mm apart: 2.25 -> 2.07
+// ms; the adjoint of 32 planes 0.1 mm apart, 1M struts: 2.11 -> 2.00 ms.  Mode 0, whose planes share their values,
 // is slower with 4 (4.45 -> 4.88 ms: twice the wave sums), and so is mode 2
 // (0.53 -> 0.60 ms).
 template <int SZ, bool SR, int MODE>
