@@ -231,7 +231,7 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
     unsigned long long n_cand = 0, n_useful = 0;
 
     const StrutRec<T>* recs = (const StrutRec<T>*)a.rec;
-    const float hxf = (float)hx, hyf = (float)hy;
+    const double sc_u = __builtin_ldexp(1.0, -__builtin_amdgcn_frexp_exp(a.R));
     for (uint32_t cbase = beg; cbase < end; cbase += kWave) {
         // ------------------------------------------------- pairs of 64 entries
         const uint32_t idx = cbase + (uint32_t)lane;
@@ -255,18 +255,27 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
         if (SZ > 1) {
             const StrutRec<T> r = recs[p];
             const double4 ln = a.line[p];
-            const double wx = cx - (double)r.ax, wy = cy - (double)r.ay,
-                         wz = a.z0 + ((double)kb + 0.5) * a.dz - (double)r.az;
+            // Lengths over a power of two near the support: the test's fourth
+            // powers of raw lengths leave float32's range from supports of 4e9 and
+            // 1e-11 units on, and infinities or zeros compare as out of reach.
+            // Scaled, a value that overflows makes err infinite (kept), and one
+            // that underflows is far within the support.
+            const double Rs = SR ? (double)r.pad : a.R;
+            const double sc = SR ? __builtin_ldexp(1.0, -__builtin_amdgcn_frexp_exp(Rs)) : sc_u;
+            const double wx = (cx - (double)r.ax) * sc, wy = (cy - (double)r.ay) * sc,
+                         wz = (a.z0 + ((double)kb + 0.5) * a.dz - (double)r.az) * sc;
+            const double dz = a.dz * sc;
+            const float hxf = (float)(hx * sc), hyf = (float)(hy * sc);
             const double tc = fma(wx, ln.x, fma(wy, ln.y, wz * ln.z));
             const double mx = fma(tc, ln.x, -wx), my = fma(tc, ln.y, -wy), mz = fma(tc, ln.z, -wz);
-            const float tc0 = (float)tc, L = (float)ln.w, ux = (float)ln.x, uy = (float)ln.y;
+            const float tc0 = (float)tc, L = (float)(ln.w * sc), ux = (float)ln.x, uy = (float)ln.y;
             const float mx0 = (float)mx, my0 = (float)my;
             const float m20 = (float)fma(mx, mx, fma(my, my, mz * mz));
-            const float dtc = (float)(a.dz * ln.z);
-            const float vx = (float)(a.dz * ln.z * ln.x), vy = (float)(a.dz * ln.z * ln.y);
-            const float c1 = (float)(-2.0 * a.dz * mz), c2 = (float)(a.dz * a.dz * (1.0 - ln.z * ln.z));
-            const float Rs = SR ? (float)r.pad : (float)a.R;
-            const float Rw2 = Rs * Rs * 1.00002f;
+            const float dtc = (float)(dz * ln.z);
+            const float vx = (float)(dz * ln.z * ln.x), vy = (float)(dz * ln.z * ln.y);
+            const float c1 = (float)(-2.0 * dz * mz), c2 = (float)(dz * dz * (1.0 - ln.z * ln.z));
+            const float Rf = (float)(Rs * sc);
+            const float Rw2 = Rf * Rf * 1.00002f;
             // what the rounding of the values below may add up to in D^2 and q
             const float T1 = fabsf(tc0) + (float)SZ * fabsf(dtc) + L;
             const float M1 = m20 + (float)SZ * fabsf(c1) + (float)(SZ * SZ) * c2;
