@@ -1021,7 +1021,7 @@ lsl_status lattice_bin(const lsl_lattice* L, const lsl_grid* G, const lsl_bin_pa
         ga.support = L->support;
         ga.kernel = L->kernel;
         ga.sigma = L->sigma;
-        ga.wq_unit = b->gauss_short ? L->sigma * std::sqrt(2.0) : 1.0;
+        ga.wq_unit = b->gauss_short ? L->sigma * std::sqrt(2.0) / kSqrtLog2E : 1.0;
         ga.rec = b->rec;
         ga.ranges = b->ranges;
         ga.pranges = b->pranges;

@@ -81,40 +81,38 @@ __device__ __forceinline__ T eval_term_gauss(const Stage<T>& e, T dX, T dY, T d2
 
 // The Gaussian term of lattices whose supports stay within kGaussNear sigma
 // (3 sigma is the usual choice), in float32.  Lengths are in units of
-// sigma sqrt 2 (the staging scales them in float64), so that H is the
-// exponent itself and the ends the erf's arguments, |x| <= h <= 2.143:
+// sigma sqrt(2 / log2 e) (the staging scales them in float64), so that H is the
+// exponent to base 2 itself, |x| <= h <= 2.577 at the ends, and
 //
-//   wq [exp(H) (F(cb) - F(ca)) - (cb - ca)],  F(x) = integral of exp(-t^2)
-//   from 0 to x = x P(x^2),
+//   wq [2^H (F(cb) - F(ca)) - (cb - ca)],  F(x) = integral of 2^(-t^2) from 0
+//   to x = x P(x^2),
 //
-// with P of degree 9 about x^2 = 2.3 (minimax fit of F(x)/x on x^2 <= 4.6,
-// relative error 2.3e-8; in float32 the error of F is at most 1.1e-7, 2.7e-8
-// in the mean square), and exp(H) = 2^t (1 + l ln 2), t + l = H log2 e in two
-// parts, from the hardware's exp2.  No branches, where erff takes both of its
-// own in most waves; bound by its instructions' issue.  16 planes of 2048^2
-// of 1M struts: 4.3 ms with erff and expf, 2.75 ms so.
+// with P of degree 10 about x^2 = 3.4375 (minimax fit of F(x)/x on x^2 <= 6.64;
+// of the centres in steps of 1/64 the one whose coefficients' rounding to
+// float32 costs least: relative error 5.3e-9, mean 9e-10, so that a sum of
+// many terms gains no bias), the difference of the two products rounded
+// once, and 2^H from the hardware's exp2 with no rounding before it.  Emulated
+// in float32 against float64, the form with erf and exp correctly rounded in
+// brackets: at supports of 3 sigma a term is 1.8e-8 of the largest off in the
+// mean square (2.1e-8), a sum of 40 terms 3.8e-8 (4.4e-8); no worse than that form
+// at any support from 0.1 to 3.03 sigma.  No branches, where erff takes both of
+// its own in most waves; bound by its instructions' issue.  16 planes of 2048^2
+// of 1M struts: 4.3 ms with erff and expf, 2.5 ms so.
 constexpr int kGaussShort = 2;                  // the kernel parameter of this form
 
-__device__ __forceinline__ float gauss_integral(float x) {
-    const float t = __builtin_fmaf(x, x, -2.3f);
-    float p = -1.9834541e-08f;
-    p = __builtin_fmaf(p, t, 2.1390387e-07f);
-    p = __builtin_fmaf(p, t, -1.7929643e-06f);
-    p = __builtin_fmaf(p, t, 1.5054211e-05f);
-    p = __builtin_fmaf(p, t, -0.00011398175f);
-    p = __builtin_fmaf(p, t, 0.00075566163f);
-    p = __builtin_fmaf(p, t, -0.0043729343f);
-    p = __builtin_fmaf(p, t, 0.022094995f);
-    p = __builtin_fmaf(p, t, -0.10117798f);
-    p = __builtin_fmaf(p, t, 0.56567758f);
-    return x * p;
-}
-
-__device__ __forceinline__ float gauss_exp(float H) {
-    const float t = H * 1.44269502f;
-    const float l = __builtin_fmaf(H, 1.92596303e-8f, __builtin_fmaf(H, 1.44269502f, -t));
-    const float e = __builtin_amdgcn_exp2f(t);
-    return __builtin_fmaf(e, l * 0.693147182f, e);
+__device__ __forceinline__ float gauss_poly(float x) {
+    const float t = __builtin_fmaf(x, x, -3.4375f);
+    float p = 4.4692621e-11f;
+    p = __builtin_fmaf(p, t, -7.0460648e-10f);
+    p = __builtin_fmaf(p, t, 9.396974e-09f);
+    p = __builtin_fmaf(p, t, -1.2787227e-07f);
+    p = __builtin_fmaf(p, t, 1.5704942e-06f);
+    p = __builtin_fmaf(p, t, -1.7079133e-05f);
+    p = __builtin_fmaf(p, t, 0.00016385793f);
+    p = __builtin_fmaf(p, t, -0.0013756008f);
+    p = __builtin_fmaf(p, t, 0.010109045f);
+    p = __builtin_fmaf(p, t, -0.067659326f);
+    return __builtin_fmaf(p, t, 0.55745947f);
 }
 
 __device__ __forceinline__ float eval_term_short(const Stage<float>& e, float dX, float dY,
@@ -127,7 +125,8 @@ __device__ __forceinline__ float eval_term_short(const Stage<float>& e, float dX
     const float h = N::sqrt_(N::max_(H, 0.0f));
     const float ca = N::clamp_(al, -h, h);
     const float cb = N::clamp_(be, -h, h);
-    return e.wq * N::fma_(gauss_exp(H), gauss_integral(cb) - gauss_integral(ca), ca - cb);
+    const float E = N::fma_(cb, gauss_poly(cb), -(ca * gauss_poly(ca)));
+    return e.wq * N::fma_(__builtin_amdgcn_exp2f(H), E, ca - cb);
 }
 
 template <typename T>
@@ -182,8 +181,8 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
                                             Stage<T>* stage, T* pend, Pairs<SZ>& pl) {
     constexpr bool kShort = K == kGaussShort;
     constexpr int G = K == LSL_KERNEL_QUARTIC ? Group<T>::n : 1;
-    // the unit of length is 1 / lu (1, or sigma sqrt 2)
-    const double lu = kShort ? a.gk1 : 1.0;
+    // the unit of length is 1 / lu (1, or the short Gaussian form's)
+    const double lu = kShort ? a.gk1 * kSqrtLog2E : 1.0;
     const int lane = lane_id();
     const uint32_t n_binned = a.n_binned, n_pairs = a.n_pairs;
     const int nsub = a.tile / kBlockPix;

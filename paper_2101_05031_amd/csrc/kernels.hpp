@@ -6,8 +6,10 @@
 namespace lsl {
 
 // The float32 Gaussian kernel's short form holds up to this support over
-// sigma: its fit of the erf ends at x^2 = 4.6, R / sigma = 3.033.
+// sigma: its fit ends at x^2 = 6.64 = 4.6 log2 e, R / sigma = 3.033.  It takes
+// lengths in units of sigma sqrt(2 / log2 e).
 constexpr double kGaussNear = 3.03;
+constexpr double kSqrtLog2E = 1.2011224087864498;
 
 // ----------------------------------------------------------------- prep.hip
 struct PrepArgs {
@@ -143,7 +145,7 @@ struct FieldArgs {
     int32_t kernel;                   // LSL_KERNEL_*
     double gk1, gk2, gc0;             // Gaussian: 1/(sigma sqrt 2), 1/(2 sigma^2), sigma sqrt(pi/2)
     int32_t gauss_short;              // float32 Gaussian: 1 = supports within kGaussNear sigma
-                                      // (lengths and weights in units of sigma sqrt 2)
+                                      // (field_block.hpp: lengths and weights in its unit)
     int32_t plane_ref;                // float32 quartic: 1 = every plane is its own
                                       // reference plane (field_q32.hpp), 0 = groups of 8
     void* field;                      // [nk][H][W] or null (not written)

@@ -250,3 +250,36 @@ def test_gauss_widths_around_the_short_form(ratio, per_strut):
     b = bin_lattice(lat, grid, slab=4)
     f = api.slice_field(b, ks.start, len(ks))
     assert_field_close(f.cpu().numpy(), oracle_field(lat, grid, ks), lat.C, 1e-5, "gauss width")
+
+
+# The float32 Gaussian's polynomial form serves lattices whose supports all stay
+# within 3.03 sigma.  One strut of a wider support, far from the planes compared,
+# puts the same lattice on erf and exp: the polynomial's error against the
+# oracle has to be no larger than theirs.
+@pytest.mark.parametrize("ratio", [0.5, 1.0, 2.0, 2.5, 3.0, 3.02])
+def test_short_gaussian_is_as_exact_as_erf(ratio):
+    square = {"short": 0.0, "erf": 0.0}
+    for seed in (21, 22, 23):
+        lat = synth.kuhn_lattice(6, 24.0, seed=seed)
+        grid = synth.grid_for(lat, 301, 283, 27, dz=0.83)
+        lat = synth.with_gauss(lat, 1.0 / ratio)
+        ks = range(9, 13)
+        ref = oracle_field(lat, grid, ks)
+        # one strut more, at the height of the last plane: binned, out of reach
+        top = grid.slice_z(grid.n_slices - 1)
+        nodes = np.concatenate([lat.nodes, [[12.0, 12.0, top], [13.0, 12.0, top]]])
+        n = lat.n_nodes
+        for what, wide in (("short", lat.R), ("erf", 3.04 * lat.sigma)):
+            one = dataclasses.replace(
+                lat, nodes=nodes.astype(np.float32), R=max(lat.R, wide),
+                edges=np.concatenate([lat.edges, [[n, n + 1]]]).astype(np.int32),
+                weight=np.append(lat.weight, 0.1).astype(np.float32),
+                support=np.append(np.full(lat.n_edges, lat.R), wide).astype(np.float32))
+            assert top - grid.slice_z(ks[-1]) > wide
+            b = bin_lattice(one, grid, tile=16, slab=4)
+            f = api.slice_field(b, ks.start, len(ks)).cpu().numpy().astype(np.float64)
+            e = (f - ref) / np.maximum(np.abs(ref), lat.C)
+            square[what] += float((e ** 2).mean())
+    rms = {k: (v / 3) ** 0.5 for k, v in square.items()}
+    print(f"R = {ratio} sigma: rms error {rms}", flush=True)
+    assert rms["short"] <= rms["erf"]
