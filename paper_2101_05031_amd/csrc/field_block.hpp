@@ -230,7 +230,8 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
     unsigned long long n_cand = 0, n_useful = 0;
 
     const StrutRec<T>* recs = (const StrutRec<T>*)a.rec;
-    const double sc_u = __builtin_ldexp(1.0, -__builtin_amdgcn_frexp_exp(a.R));
+    constexpr bool kScale = sizeof(T) == 8 || K != LSL_KERNEL_QUARTIC;
+    const double sc_u = kScale ? __builtin_ldexp(1.0, -__builtin_amdgcn_frexp_exp(a.R)) : 1.0;
     for (uint32_t cbase = beg; cbase < end; cbase += kWave) {
         // ------------------------------------------------- pairs of 64 entries
         const uint32_t idx = cbase + (uint32_t)lane;
@@ -258,9 +259,13 @@ __device__ __forceinline__ void field_block(const FieldArgs& a, int slab, int tx
             // powers of raw lengths leave float32's range from supports of 4e9 and
             // 1e-11 units on, and infinities or zeros compare as out of reach.
             // Scaled, a value that overflows makes err infinite (kept), and one
-            // that underflows is far within the support.
+            // that underflows is far within the support.  (Not where the record's
+            // r / R^4 has a narrower range of its own, float32 and the paper's
+            // kernel: there the scaling cost 1%.)
             const double Rs = SR ? (double)r.pad : a.R;
-            const double sc = SR ? __builtin_ldexp(1.0, -__builtin_amdgcn_frexp_exp(Rs)) : sc_u;
+            const double sc = !kScale ? 1.0
+                              : SR    ? __builtin_ldexp(1.0, -__builtin_amdgcn_frexp_exp(Rs))
+                                      : sc_u;
             const double wx = (cx - (double)r.ax) * sc, wy = (cy - (double)r.ay) * sc,
                          wz = (a.z0 + ((double)kb + 0.5) * a.dz - (double)r.az) * sc;
             const double dz = a.dz * sc;
