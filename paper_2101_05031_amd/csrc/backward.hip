@@ -461,54 +461,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
 // components are of the size of the support (three more operations per
 // pair; for pixels coarse against the support this halves the error of the
 // node gradients).
-// Wave sums.  A staged pair's pixel sums are needed as kRaw raw sums over the
-// wave (G I, G phi at both ends and, for K_b and K_a, sum G K, sum (k - r) G K,
-// sum G K d_x and sum G K d_y): the three components of sum G K q_perp are
-// linear in them, so they are formed after the pass, for all its pairs at
-// once, one pair per lane, instead of per candidate by every lane before the
-// sums: a tuning
-// step of 115k struts 2.52 -> 2.46 ms.  (Summing the registers with matrix instructions, a
-// column of ones as the second operand, left the vector ALU a third of the
-// work but took eleven 32-cycle instructions per candidate: 10-20% slower.)
 namespace b32 {
-
-constexpr int kRaw = 11;
-typedef float lds_float __attribute__((may_alias));
-
-// Totals of the raw sums over the wave: lane l is left with value
-// raw_index(l).  As in reduce8, for three values more: two folds put eight
-// values, then three, on the rows of a register.
-__device__ __forceinline__ int raw_index(int lane) {
-    if (!(lane & 1)) return scatter_index(lane);
-    const int row = lane >> 4;                     // rows: values 8 10 9 10
-    return row == 0 ? 8 : row == 2 ? 9 : 10;
-}
-
-__device__ __forceinline__ float wave_totals(const float (&v)[kRaw], int lane) {
-    const float y = reduce8(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], lane);
-    const float x = fold16(fold32(v[8], v[9]), fold32(v[10], v[10]));
-    float t = x + dpp_take<0x128, 0xF>(x);         // row_ror:8
-    t += dpp_take<0xB1, 0xF>(t);
-    t += dpp_take<0x4E, 0xF>(t);
-    t += dpp_take<0x141, 0xF>(t);
-    return (lane & 1) ? t : y;
-}
-
-// room for the raw sums of kernels whose staged values do not hold them
-template <int N, int CH>
-struct Spare {
-    float spare[N][CH];
-    __device__ __forceinline__ lds_float* spare_at(int q) { return (lds_float*)&spare[q][0]; }
-};
-template <int CH>
-struct Spare<0, CH> {
-    __device__ __forceinline__ lds_float* spare_at(int) { return nullptr; }
-};
 
 template <int SZ, bool PR, int CH>
 struct Lds;
 template <int SZ, int CH>
-struct Lds<SZ, false, CH> : Spare<SZ >= 8 ? 0 : kRaw + 1, CH> {
+struct Lds<SZ, false, CH> {
     float pg[SZ][CH];         // per plane: G_k
     float4 gr[CH];            // A_0, B_0, 2 m_0,x / R^2, 2 m_0,y / R^2
     float4 e[CH];             // u_x / R, u_y / R, c1, 1 / R^2
@@ -516,21 +474,12 @@ struct Lds<SZ, false, CH> : Spare<SZ >= 8 ? 0 : kRaw + 1, CH> {
     float4 m0[CH];            // m_0 (x, y, z), R
     float4 u4[CH];            // u (x, y, z), dz u_z
     uint32_t mask[CH];        // reach bits: sub-block s, plane k at bit s SZ + k
-    uint32_t cand[CH];        // staged lane | region << 16
+    uint32_t cand[CH];        // staged lane | entry << 8 | region << 16
     float slot[CH][kParts];   // per bucket entry of the chunk
     uint8_t pairs[256];       // (entry, region) pairs: entry | region in group << log2(CH)
-    // Raw sum q of staged pair e at raw(q) + e * raw_step(q): over the pair's
-    // staged values, which have been used by then (G_k and e; `spare` where
-    // there are fewer than eight planes).
-    __device__ __forceinline__ lds_float* raw(int q) {
-        if (SZ >= 8 && q < 8) return (lds_float*)&pg[q < SZ ? q : 0][0];
-        if (SZ >= 8) return (lds_float*)&e[0] + (q - 8 < 3 ? q - 8 : 3);
-        return this->spare_at(q < kRaw ? q : kRaw);
-    }
-    __device__ __forceinline__ static int raw_step(int q) { return SZ >= 8 && q >= 8 ? 4 : 1; }
 };
 template <int SZ, int CH>
-struct Lds<SZ, true, CH> : Spare<SZ >= 4 ? 0 : kRaw + 1, CH> {
+struct Lds<SZ, true, CH> {
     float4 pl[SZ][CH];        // per plane: A_k, B_k, G_k, 2 m_k,x / R^2
     float pmy[SZ][CH];        // per plane: 2 m_k,y / R^2
     float4 e[CH];
@@ -541,12 +490,6 @@ struct Lds<SZ, true, CH> : Spare<SZ >= 4 ? 0 : kRaw + 1, CH> {
     uint32_t cand[CH];
     float slot[CH][kParts];
     uint8_t pairs[256];
-    // (over pl with four planes and more)
-    __device__ __forceinline__ lds_float* raw(int q) {
-        if (SZ >= 4) return (lds_float*)&pl[(q >> 2) < SZ ? q >> 2 : 0][0] + (q & 3);
-        return this->spare_at(q < kRaw ? q : kRaw);
-    }
-    __device__ __forceinline__ static int raw_step(int) { return SZ >= 4 ? 4 : 1; }
 };
 
 // MODE 0: 16x16 regions, shared reference planes; 1: 16x16 regions, every
@@ -614,9 +557,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
     const StrutRec<float>* recs = (const StrutRec<float>*)a.rec;
     const float* grad = (const float*)a.grad;
     float* part = (float*)a.partial;
-    // where this lane puts the raw sum it ends up with
-    lds_float* const raw_to = L.raw(raw_index(lane));
-    const int raw_step = Lds<SZ, PR, kCh>::raw_step(raw_index(lane));
+    const int own = deposit_owner(lane);
     // a pixel's place from its sub-block's first one
     const uint32_t lane_at = (uint32_t)ly * (uint32_t)a.W + (uint32_t)lx;
 
@@ -820,7 +761,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
                         if (mask != 0u) {
                             const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
                                 (uint32_t)(cm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cm, 0u));
-                            L.cand[rank] = (uint32_t)lane | ((uint32_t)rgl << 16);
+                            L.cand[rank] = (uint32_t)lane | (ent << 8) | ((uint32_t)rgl << 16);
                         }
                         n_cand = __popcll(cm);
                     }
@@ -982,81 +923,57 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
                                 }
                             });
                         });
-                        // the raw sums: over all sub-blocks, and weighted by the
-                        // pixel's d = (Dx, Dy)
-                        float v[kRaw];
-                        v[0] = Aw;
+                        // over all sub-blocks, the right-hand ones and the lower ones
+                        const float4 M = L.m0[e];
+                        const float dmx = U.w * U.x, dmy = U.w * U.y, dmz = __builtin_fmaf(U.w, U.z, -dzf);
+                        const float rux = M.w * U.x, ruy = M.w * U.y, ruz = M.w * U.z;
+                        // sum G K q_perp = m_r sum G K + dm sum (k - r) G K - sum G K d
+                        // + R u sum G K (d.u^), dm = dz u_z u - dz e_z, for K_b and K_a
+                        float v[kParts];
+                        v[0] = Aw * (1.0f / 16.0f);
                         v[1] = Aa;
                         v[2] = Ab;
-                        v[4] = ABk;
-                        v[8] = AAk;
                         if constexpr (NS == 2) {
-                            const float Bl = Bs[0] + Bs[2], Br = Bs[1] + Bs[3];
-                            const float Al = As[0] + As[2], Ar = As[1] + As[3];
-                            v[3] = Bl + Br;
-                            v[7] = Al + Ar;
-                            v[5] = __builtin_fmaf(Dx[1], Br, Dx[0] * Bl);
-                            v[9] = __builtin_fmaf(Dx[1], Ar, Dx[0] * Al);
-                            v[6] = __builtin_fmaf(Dy[1], Bs[2] + Bs[3], Dy[0] * (Bs[0] + Bs[1]));
-                            v[10] = __builtin_fmaf(Dy[1], As[2] + As[3], Dy[0] * (As[0] + As[1]));
+                            // over all sub-blocks, the right-hand and the lower ones
+                            // (d of sub-block (sx, sy) = d_00 + 8 (sx dx, sy dy))
+                            const float SXB = Bs[1] + Bs[3], SXA = As[1] + As[3];
+                            const float SYB = Bs[2] + Bs[3], SYA = As[2] + As[3];
+                            const float AB = (Bs[0] + Bs[2]) + SXB, AA = (As[0] + As[2]) + SXA;
+                            const float ABx = __builtin_fmaf(8.0f * dxf, SXB, Dx[0] * AB);
+                            const float ABy = __builtin_fmaf(8.0f * dyf, SYB, Dy[0] * AB);
+                            const float ABu = __builtin_fmaf(e8x, SXB, __builtin_fmaf(e8y, SYB, du0 * AB));
+                            const float AAx = __builtin_fmaf(8.0f * dxf, SXA, Dx[0] * AA);
+                            const float AAy = __builtin_fmaf(8.0f * dyf, SYA, Dy[0] * AA);
+                            const float AAu = __builtin_fmaf(e8x, SXA, __builtin_fmaf(e8y, SYA, du0 * AA));
+                            v[3] = __builtin_fmaf(M.x, AB, __builtin_fmaf(dmx, ABk, __builtin_fmaf(rux, ABu, -ABx)));
+                            v[4] = __builtin_fmaf(M.y, AB, __builtin_fmaf(dmy, ABk, __builtin_fmaf(ruy, ABu, -ABy)));
+                            v[5] = __builtin_fmaf(M.z, AB, __builtin_fmaf(dmz, ABk, ruz * ABu));
+                            v[6] = __builtin_fmaf(M.x, AA, __builtin_fmaf(dmx, AAk, __builtin_fmaf(rux, AAu, -AAx)));
+                            v[7] = __builtin_fmaf(M.y, AA, __builtin_fmaf(dmy, AAk, __builtin_fmaf(ruy, AAu, -AAy)));
+                            v[8] = __builtin_fmaf(M.z, AA, __builtin_fmaf(dmz, AAk, ruz * AAu));
                         } else {
-                            v[3] = Bs[0];
-                            v[7] = As[0];
-                            v[5] = Dx[0] * Bs[0];
-                            v[9] = Dx[0] * As[0];
-                            v[6] = Dy[0] * Bs[0];
-                            v[10] = Dy[0] * As[0];
-                        }
-                        raw_to[(int)e * raw_step] = wave_totals(v, lane);
-                    }
-                    __builtin_amdgcn_wave_barrier();
-
-                    // ------------------------------------------------ pair sums
-                    // sum G K q_perp = m_r sum G K + dm sum (k - r) G K - sum G K d
-                    // + u sum G K (d.u), dm = dz u_z u - dz e_z, for K_b and K_a; one
-                    // staged pair per lane, added to the entries' slots in region
-                    // order (an entry has one pair per region)
-                    float pv[kParts];
-                    const bool on = st_ok && L.mask[lane & (kCh - 1)] != 0u;
-                    if (on) {
-                        float x[kRaw];
-                        for (int q = 0; q < kRaw; ++q)
-                            x[q] = L.raw(q)[lane * Lds<SZ, PR, kCh>::raw_step(q)];
-                        const float4 M = L.m0[lane], U = L.u4[lane];
-                        const double ux = U.x, uy = U.y, uz = U.z;
-                        const double dmx = (double)U.w * ux, dmy = (double)U.w * uy,
-                                     dmz = (double)U.w * uz - a.dz;
-                        double t[2][3];
-                        for (int f = 0; f < 2; ++f) {
-                            const double S = x[3 + 4 * f], Sk = x[4 + 4 * f], Sx = x[5 + 4 * f],
-                                         Sy = x[6 + 4 * f];
-                            const double Su = fma(ux, Sx, uy * Sy);
-                            t[f][0] = fma((double)M.x, S, fma(dmx, Sk, fma(ux, Su, -Sx)));
-                            t[f][1] = fma((double)M.y, S, fma(dmy, Sk, fma(uy, Su, -Sy)));
-                            t[f][2] = fma((double)M.z, S, fma(dmz, Sk, uz * Su));
+                            // one sub-block: the lane's q_perp at plane r, m_r - d + (d.u) u,
+                            // weights both ends' sums
+                            const float qx = __builtin_fmaf(rux, du0, M.x - Dx[0]);
+                            const float qy = __builtin_fmaf(ruy, du0, M.y - Dy[0]);
+                            const float qz = __builtin_fmaf(ruz, du0, M.z);
+                            v[3] = __builtin_fmaf(qx, Bs[0], dmx * ABk);
+                            v[4] = __builtin_fmaf(qy, Bs[0], dmy * ABk);
+                            v[5] = __builtin_fmaf(qz, Bs[0], dmz * ABk);
+                            v[6] = __builtin_fmaf(qx, As[0], dmx * AAk);
+                            v[7] = __builtin_fmaf(qy, As[0], dmy * AAk);
+                            v[8] = __builtin_fmaf(qz, As[0], dmz * AAk);
                         }
                         if constexpr (MODE == 0) {
                             // K_a = K_b + 2 J L: the second sums carried J
-                            const float4 Rg = L.gr[lane];
-                            const double Lh = (double)Rg.y - (double)Rg.x;
-                            for (int q = 0; q < 3; ++q) t[1][q] = fma(Lh, t[1][q], t[0][q]);
+                            const float Lh = Rg.y - Rg.x;
+                            v[6] = __builtin_fmaf(Lh, v[6], v[3]);
+                            v[7] = __builtin_fmaf(Lh, v[7], v[4]);
+                            v[8] = __builtin_fmaf(Lh, v[8], v[5]);
                         }
-                        pv[0] = x[0] * (1.0f / 16.0f);
-                        pv[1] = x[1];
-                        pv[2] = x[2];
-                        for (int q = 0; q < 3; ++q) {
-                            pv[3 + q] = (float)t[0][q];
-                            pv[6 + q] = (float)t[1][q];
-                        }
+                        deposit(L.slot[(c >> 8) & 0xffu], v, lane, own);
                     }
-                    const int m_pairs = npair - pb < kCh ? npair - pb : kCh;
-                    const int rg0 = __builtin_amdgcn_readlane(rgl, 0);
-                    const int rg1 = __builtin_amdgcn_readlane(rgl, m_pairs - 1);
-                    for (int rg = rg0; rg <= rg1; ++rg) {
-                        if (on && rgl == rg)
-                            for (int q = 0; q < kParts; ++q) L.slot[ent][q] += pv[q];
-                        __builtin_amdgcn_wave_barrier();
-                    }
+                    __builtin_amdgcn_wave_barrier();
                 }
             }
         }

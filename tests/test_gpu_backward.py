@@ -305,3 +305,31 @@ def test_d4_gradients_vs_finite_differences():
     print(f"D4 FD: worst per-parameter {per.max():.2e}, median {np.median(per):.2e}, "
           f"normwise {norm:.2e}", flush=True)
     assert per.max() <= 1e-4 and norm <= 1e-4
+
+
+# The node gradients' float32 error, normwise against the oracle, averaged over
+# four lattices (fine pixels: one): pixels of 0.03 supports (16x16 regions, shared reference planes) and
+# of 0.35 to 1 supports (8x8 regions), where the line's offset from a pixel is far
+# smaller than the pixel's from the region's centre.  The bounds are 5% above what
+# offsets formed per pixel, before any sum, measured on these inputs; sums whose
+# offsets are subtracted afterwards lie 12 to 34% above it.
+@pytest.mark.parametrize("pixel,pitch,measured", [
+    (0.03, 0.05, 1.02e-7), (0.35, 0.5, 1.44e-7), (0.5, 0.5, 1.54e-7), (0.7, 0.5, 2.35e-7),
+    (1.0, 0.5, 2.68e-7)])
+def test_node_gradient_error_of_coarse_and_fine_pixels(pixel, pitch, measured):
+    size = 12.0 if pixel < 0.1 else 24.0
+    err = []
+    for seed in (1,) if pixel < 0.1 else (1, 2, 3, 4):
+        lat = synth.kuhn_lattice(6, size, seed=seed)
+        d = pixel * lat.R
+        W = int((size + 2 * lat.R) / d) + 4
+        grid = synth.Grid(-lat.R - 2 * d, -lat.R - 1.9 * d, d, d, W, W + 1,
+                          3.0 if pixel < 0.1 else 0.0, pitch * lat.R, 16)
+        G = np.random.default_rng(seed + 50).normal(size=(16, grid.H, grid.W)).astype(np.float32)
+        print(f"pixel {pixel} R, seed {seed}: {grid.W} x {grid.H}", flush=True)
+        b = bin_lattice(lat, grid, tile=32, slab=8)
+        _, gn = api.slice_field_backward(b, 0, 16, torch.from_numpy(G).cuda())
+        _, rn = OG.slice_vjp(lat.nodes, lat.edges, lat.weight, lat.R, grid, range(16), G)
+        err.append(np.linalg.norm(gn.cpu().numpy() - rn) / np.linalg.norm(rn))
+    print(f"pixel {pixel} R: node gradients' error {np.mean(err):.3e}", flush=True)
+    assert np.mean(err) <= 1.05 * measured
