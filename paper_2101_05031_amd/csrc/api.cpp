@@ -1543,7 +1543,7 @@ lsl_status build_queue(lattice_bins* b, const FieldArgs& a, const uint32_t** que
 struct GraphShape {
     int32_t dtype, kernel, gauss_short, strut_R, plane_ref, slab, planes, tile, phase;
     int32_t field, bits, segs, slot;
-    int32_t sort, launches, scan;      // which launches the phases make
+    int32_t sort, launches, scan, emits;   // which launches the phases make
 };
 
 // Enqueues one phase of a group's part of slice_batch on `st`:
@@ -1781,7 +1781,8 @@ lsl_status slice_batch(lattice_bins* b, int32_t k0, int32_t nk, void* field, uin
                              (int32_t)((n_call_groups - 1) & 1),
                              radix_form(n_items),
                              (int32_t)field_launches(b->tile, n_items),
-                             scan_form((size_t)nkg * (size_t)((b->grid.H + 7) / 8) + 1)};
+                             scan_form((size_t)nkg * (size_t)((b->grid.H + 7) / 8) + 1),
+                             (int32_t)contour_launches(nkg, b->grid.W, b->grid.H)};
             std::vector<unsigned char> key((unsigned char*)&shape,
                                            (unsigned char*)&shape + sizeof(shape));
             cs = GraphCache::get().launch(key, gr[ph], st);

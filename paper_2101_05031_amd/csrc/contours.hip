@@ -30,6 +30,7 @@
 // Outputs are deterministic and written with no atomics.
 #include <algorithm>
 
+#include "grid.hpp"
 #include "kernels.hpp"
 
 namespace lsl {
@@ -278,7 +279,8 @@ __device__ __forceinline__ float2 seg_end(const int8_t* g, int i, int j, int32_t
 constexpr uint32_t kList = 512;        // segments listed per wave and round
 
 template <bool SUB, typename T>
-__global__ __launch_bounds__(kMThreads) void k_strip_emit(const uint64_t* img, uint64_t n_chunks,
+__global__ __launch_bounds__(kMThreads) void k_strip_emit(uint64_t block0, const uint64_t* img,
+                                                          uint64_t n_chunks,
                                                           int32_t W, int32_t H,
                                                           const unsigned long long* scan,
                                                           const unsigned long long* rows,
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(kMThreads) void k_strip_emit(const uint64_t* img, u
     __shared__ uint64_t s_shift[kMThreads / kWave][8];
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const int nbx = (W + 7) / 8, nby = (H + 7) / 8, nch = (nbx + kWave - 1) / kWave;
-    const uint64_t item = (uint64_t)blockIdx.x * (kMThreads / kWave) + (uint64_t)w;
+    const uint64_t item = (block0 + blockIdx.x) * (kMThreads / kWave) + (uint64_t)w;
     if (item >= n_chunks) return;
     const uint64_t all[2] = {crows[2 * item], crows[2 * item + 1]};
     if ((all[0] | all[1]) == 0ull) return;
@@ -809,15 +811,19 @@ unsigned long long* strip_rows(unsigned long long* tmp, size_t n) {
 unsigned long long* chunk_rows(unsigned long long* tmp, size_t n) {
     return strip_rows(tmp, n) + 4 * n;
 }
+uint64_t emit_blocks(size_t chunks) { return (chunks + kMThreads / kWave - 1) / (kMThreads / kWave); }
+
 template <bool SUB, typename T>
 void emit_launch(const uint64_t* img, size_t n, int32_t W, int32_t H,
                  const unsigned long long* tmp, const unsigned long long* base, float* segs,
                  int64_t capacity, const SubPix& sp, hipStream_t st) {
     unsigned long long* t = (unsigned long long*)tmp;
     const size_t chunks = n * strip_chunks(W);
-    k_strip_emit<SUB, T><<<(unsigned)((chunks + 3) / 4), kMThreads, 0, st>>>(
-        img, chunks, W, H, tmp, strip_rows(t, n), chunk_rows(t, n), base, (float4*)segs, capacity,
-        sp);
+    for_launches(emit_blocks(chunks), kMThreads, [&](uint64_t block0, uint32_t blocks) {
+        k_strip_emit<SUB, T><<<blocks, kMThreads, 0, st>>>(
+            block0, img, chunks, W, H, tmp, strip_rows(t, n), chunk_rows(t, n), base,
+            (float4*)segs, capacity, sp);
+    });
 }
 }  // namespace
 
@@ -869,6 +875,11 @@ lsl_status launch_contours_emit(const uint64_t* img, int32_t nk, int32_t W, int3
     if (base) k_ms_advance<<<1, 64, 0, st>>>(base, tmp, n);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
+}
+
+uint32_t contour_launches(int32_t nk, int32_t W, int32_t H) {
+    const size_t n = (size_t)nk * (size_t)((H + 7) / 8);
+    return (uint32_t)launch_count(emit_blocks(n * strip_chunks(W)), kMThreads);
 }
 
 lsl_status launch_bits_rows(const uint64_t* img, int32_t nk, int32_t W, int32_t H,

@@ -214,6 +214,8 @@ lsl_status launch_contours_count(const uint64_t* img, int32_t nk, int32_t W, int
 lsl_status launch_contours_emit(const uint64_t* img, int32_t nk, int32_t W, int32_t H,
                                 const unsigned long long* tmp, unsigned long long* base,
                                 float* segs, int64_t capacity, hipStream_t st);
+// launches the emit pass makes
+uint32_t contour_launches(int32_t nk, int32_t W, int32_t H);
 // Sub-pixel segments of nk planes (same cells and order as the emit pass;
 // tmp, offsets from launch_contours_count with no base) and, if chain and
 // rank are given, each segment's chain head and rank within its plane.

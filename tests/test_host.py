@@ -78,3 +78,38 @@ def test_bench_refuses_several_gpus():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in json.loads(r.stdout.strip().splitlines()[-1])["error"]
+
+
+def test_launches_cover_a_grid(tmp_path):
+    """csrc/grid.hpp: the launches of a grid cover its blocks once, in order,
+    each within 2^32 threads."""
+    src = tmp_path / "grid.cpp"
+    src.write_text("""
+        #include "grid.hpp"
+        #include <cstdio>
+        #include <initializer_list>
+        int main() {
+            for (uint32_t threads : {64u, 256u, 1024u})
+                for (uint64_t n : {0ull, 1ull, 1000ull, (1ull << 31) / threads - 1,
+                                   (1ull << 31) / threads, (1ull << 31) / threads + 1,
+                                   (1ull << 32) / threads, 5 * ((1ull << 32) / threads) + 7}) {
+                    uint64_t at = 0, calls = 0;
+                    bool ok = true;
+                    lsl::for_launches(n, threads, [&](uint64_t b0, uint32_t blocks) {
+                        ok = ok && b0 == at && blocks > 0 &&
+                             (uint64_t)blocks * threads <= 0xffffffffull;
+                        at += blocks;
+                        ++calls;
+                    });
+                    if (!ok || at != n || calls != lsl::launch_count(n, threads)) {
+                        std::printf("%u threads, %llu blocks\\n", threads, (unsigned long long)n);
+                        return 1;
+                    }
+                }
+            return 0;
+        }
+    """)
+    exe = tmp_path / "grid"
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2101_05031_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    subprocess.run([str(exe)], check=True)
