@@ -45,6 +45,7 @@
 // (slab, tile), and the nodes gather their struts' gradients through a node
 // -> strut incidence list.  Every reduction has a fixed order.
 #include "field_q32.hpp"
+#include "grid.hpp"
 #include "kernels.hpp"
 
 namespace lsl {
@@ -184,7 +185,7 @@ __device__ __forceinline__ int deposit_owner(int lane) {
 }
 
 template <typename T, int SZ, bool SR>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_backward(BackArgs a, uint32_t n_items) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_backward(BackArgs a, uint32_t item0) {
     // compacted list of the struts that reach the current block
     __shared__ T bs_ux[kChunk], bs_uy[kChunk], bs_uz[kChunk];
     __shared__ T bs_m0[3][kChunk], bs_dm[3][kChunk];   // m at the slab's first plane, step per plane
@@ -193,8 +194,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     __shared__ T slot[kChunk][kParts];
 
     const int lane = lane_id();
-    if (blockIdx.x >= n_items) return;
-    uint32_t t = a.queue[blockIdx.x];
+    uint32_t t = a.queue[item0 + blockIdx.x];
     const int tx = (int)(t % (uint32_t)a.ntx);
     t /= (uint32_t)a.ntx;
     const int ty = (int)(t % (uint32_t)a.nty);
@@ -506,7 +506,7 @@ struct Lds<SZ, true, CH> {
 template <int SZ, bool SR, int MODE>
 __global__ __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
-    BackArgs a, uint32_t n_items) {
+    BackArgs a, uint32_t item0) {
     constexpr int NS = MODE == 2 ? 1 : 2;     // sub-blocks per region side
     constexpr bool PR = MODE != 0;            // per-plane values in LDS
     constexpr bool QD = MODE == 2;            // H^ from q_perp
@@ -517,12 +517,11 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
     constexpr int kCh = MODE == 2 ? 32 : kWave;
     __shared__ Lds<SZ, PR, kCh> L;
     const int lane = lane_id();
-    if (blockIdx.x >= n_items) return;
     // the items in descending cost order, handed out by the hardware as others
     // end: a bucket is a long item (a few to a wave's place), and the last
     // ones to run had better be short: 27 planes of 1021 x 1027 in 16640
     // buckets 0.70 -> 0.54 ms, 32 planes of 2048^2 in 16384 4.90 -> 4.44 ms
-    uint32_t t = a.queue[blockIdx.x];
+    uint32_t t = a.queue[item0 + blockIdx.x];
     const int tx = (int)(t % (uint32_t)a.ntx);
     t /= (uint32_t)a.ntx;
     const int ty = (int)(t % (uint32_t)a.nty);
@@ -988,32 +987,32 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
 }
 
 template <int SZ, bool SR>
-void launch_sz(const BackArgs& a, uint32_t n_items, hipStream_t st) {
+void launch_sz(const BackArgs& a, uint32_t item0, uint32_t n, hipStream_t st) {
     if (!a.wide)
-        k_backward32<SZ, SR, 2><<<n_items, 64, 0, st>>>(a, n_items);
+        k_backward32<SZ, SR, 2><<<n, 64, 0, st>>>(a, item0);
     else if (a.plane_ref)
-        k_backward32<SZ >= 8 ? 4 : SZ, SR, 1><<<n_items, 64, 0, st>>>(a, n_items);
+        k_backward32<SZ >= 8 ? 4 : SZ, SR, 1><<<n, 64, 0, st>>>(a, item0);
     else
-        k_backward32<SZ, SR, 0><<<n_items, 64, 0, st>>>(a, n_items);
+        k_backward32<SZ, SR, 0><<<n, 64, 0, st>>>(a, item0);
 }
 
 template <int SZ>
-void launch_sr(const BackArgs& a, uint32_t n_items, hipStream_t st) {
+void launch_sr(const BackArgs& a, uint32_t item0, uint32_t n, hipStream_t st) {
     if (a.strut_R)
-        launch_sz<SZ, true>(a, n_items, st);
+        launch_sz<SZ, true>(a, item0, n, st);
     else
-        launch_sz<SZ, false>(a, n_items, st);
+        launch_sz<SZ, false>(a, item0, n, st);
 }
 
-lsl_status launch(const BackArgs& a, uint32_t n_items, hipStream_t st) {
+lsl_status launch(const BackArgs& a, uint32_t item0, uint32_t n, hipStream_t st) {
     if (a.slab <= 1)
-        launch_sr<1>(a, n_items, st);
+        launch_sr<1>(a, item0, n, st);
     else if (a.slab <= 2)
-        launch_sr<2>(a, n_items, st);
+        launch_sr<2>(a, item0, n, st);
     else if (a.slab <= 4)
-        launch_sr<4>(a, n_items, st);
+        launch_sr<4>(a, item0, n, st);
     else
-        launch_sr<8>(a, n_items, st);      // longer slabs: windows of 8 planes (mode 1: 4)
+        launch_sr<8>(a, item0, n, st);      // longer slabs: windows of 8 planes (mode 1: 4)
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }
@@ -1030,12 +1029,12 @@ lsl_status launch(const BackArgs& a, uint32_t n_items, hipStream_t st) {
 constexpr int kRedStruts = 8;
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_reduce(ReduceArgs a, const SRange* ranges, int32_t sa,
-                                                int32_t s_lo, int32_t s_hi, uint32_t n_pairs,
+__global__ __launch_bounds__(256) void k_reduce(uint32_t block0, ReduceArgs a,
+                                                const SRange* ranges, int32_t sa, int32_t s_lo, int32_t s_hi, uint32_t n_pairs,
                                                 uint32_t n_binned) {
     __shared__ double sums[4][kRedStruts][kParts];
     const int lane = lane_id(), w = wave_index();
-    const uint32_t i0 = (blockIdx.x * 4u + (uint32_t)w) * kRedStruts;
+    const uint32_t i0 = ((block0 + blockIdx.x) * 4u + (uint32_t)w) * kRedStruts;
     if (i0 >= a.n_active) return;
     const T* part = (const T*)a.partial;
     const int n_here = a.n_active - i0 < (uint32_t)kRedStruts ? (int)(a.n_active - i0) : kRedStruts;
@@ -1142,22 +1141,22 @@ __global__ void k_fill_t(T* p, size_t n) {
 }
 
 template <typename T, int SZ>
-lsl_status launch_b(const BackArgs& a, uint32_t n_items, hipStream_t st) {
+lsl_status launch_b(const BackArgs& a, uint32_t item0, uint32_t n, hipStream_t st) {
     if (a.strut_R)
-        k_backward<T, SZ, true><<<n_items, 64, 0, st>>>(a, n_items);
+        k_backward<T, SZ, true><<<n, 64, 0, st>>>(a, item0);
     else
-        k_backward<T, SZ, false><<<n_items, 64, 0, st>>>(a, n_items);
+        k_backward<T, SZ, false><<<n, 64, 0, st>>>(a, item0);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }
 
 template <typename T>
-lsl_status launch_bt(const BackArgs& a, uint32_t n_items, hipStream_t st) {
-    if (a.slab <= 1) return launch_b<T, 1>(a, n_items, st);
-    if (a.slab <= 2) return launch_b<T, 2>(a, n_items, st);
-    if (a.slab <= 4) return launch_b<T, 4>(a, n_items, st);
-    if (a.slab <= 8) return launch_b<T, 8>(a, n_items, st);
-    return launch_b<T, 16>(a, n_items, st);
+lsl_status launch_bt(const BackArgs& a, uint32_t item0, uint32_t n, hipStream_t st) {
+    if (a.slab <= 1) return launch_b<T, 1>(a, item0, n, st);
+    if (a.slab <= 2) return launch_b<T, 2>(a, item0, n, st);
+    if (a.slab <= 4) return launch_b<T, 4>(a, item0, n, st);
+    if (a.slab <= 8) return launch_b<T, 8>(a, item0, n, st);
+    return launch_b<T, 16>(a, item0, n, st);
 }
 
 }  // namespace
@@ -1169,19 +1168,24 @@ lsl_status launch_backward(int dtype, const BackArgs& a, hipStream_t st) {
         set_error("slice_field_backward: too many work items in one launch");
         return LSL_EINTERNAL;
     }
-    if (dtype == LSL_F32) return b32::launch(a, (uint32_t)n_items, st);
-    return launch_bt<double>(a, (uint32_t)n_items, st);
+    lsl_status s = LSL_OK;
+    for_launches(n_items, 64, [&](uint64_t item0, uint32_t n) {
+        if (s != LSL_OK) return;
+        s = dtype == LSL_F32 ? b32::launch(a, (uint32_t)item0, n, st)
+                             : launch_bt<double>(a, (uint32_t)item0, n, st);
+    });
+    return s;
 }
 
 lsl_status launch_reduce(int dtype, const ReduceArgs& a, const SRange* ranges, int32_t sa,
                          int32_t s_lo, int32_t s_hi, uint32_t n_pairs, uint32_t n_binned,
                          hipStream_t st) {
     if (a.n_active == 0) return LSL_OK;
-    const unsigned g = (a.n_active + 4 * kRedStruts - 1) / (4 * kRedStruts);
-    if (dtype == LSL_F32)
-        k_reduce<float><<<g, 256, 0, st>>>(a, ranges, sa, s_lo, s_hi, n_pairs, n_binned);
-    else
-        k_reduce<double><<<g, 256, 0, st>>>(a, ranges, sa, s_lo, s_hi, n_pairs, n_binned);
+    const uint64_t g = ((uint64_t)a.n_active + 4 * kRedStruts - 1) / (4 * kRedStruts);
+    for_launches(g, 256, [&](uint64_t block0, uint32_t blocks) {
+        (dtype == LSL_F32 ? k_reduce<float> : k_reduce<double>)<<<blocks, 256, 0, st>>>(
+            (uint32_t)block0, a, ranges, sa, s_lo, s_hi, n_pairs, n_binned);
+    });
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }

@@ -16,6 +16,7 @@
 // The adjoint also needs each entry's emission index (its position in the
 // strut-major order of the pairs), which group_emi rebuilds from the entry's
 // bucket and the strut's box.
+#include "grid.hpp"
 #include "kernels.hpp"
 
 namespace lsl {
@@ -122,12 +123,12 @@ __global__ void k_pair_counts(uint32_t* active, uint32_t n, const SRange* rg, in
 constexpr uint32_t kEmitFew = 65536;
 
 template <int PER>
-__global__ __launch_bounds__(256) void k_cell_emit(const uint32_t* active, uint32_t n,
+__global__ __launch_bounds__(256) void k_cell_emit(uint32_t block0, const uint32_t* active, uint32_t n,
                                                    const SRange* rg, int32_t sa, int32_t nty,
                                                    int32_t nseg, const uint32_t* toff,
                                                    uint32_t* keys, uint32_t* vals, uint32_t cap) {
     const int lane = lane_id();
-    const uint32_t a0 = ((blockIdx.x * blockDim.x + threadIdx.x) / kWave) * PER;
+    const uint32_t a0 = ((block0 + blockIdx.x) * 4u + threadIdx.x / kWave) * PER;
     if (a0 >= n) return;
     const uint32_t a = a0 + lane;
     SRange r{0, 0, 0, 0, 0, -1};
@@ -243,9 +244,9 @@ __global__ void k_csr_offsets(const uint32_t* keys, uint32_t n, uint32_t n_bucke
 
 // keys[i] = b for every entry i of bucket b: one wave per bucket, its lanes
 // writing consecutive entries
-__global__ __launch_bounds__(256) void k_expand_keys(const uint32_t* offsets, uint32_t n_buckets,
-                                                     uint32_t* keys) {
-    const uint32_t b = blockIdx.x * 4u + (threadIdx.x >> 6);
+__global__ __launch_bounds__(256) void k_expand_keys(uint32_t block0, const uint32_t* offsets,
+                                                     uint32_t n_buckets, uint32_t* keys) {
+    const uint32_t b = (block0 + blockIdx.x) * 4u + (threadIdx.x >> 6);
     if (b >= n_buckets) return;
     const uint32_t e = offsets[b + 1];
     for (uint32_t i = offsets[b] + (uint32_t)lane_id(); i < e; i += kWave) keys[i] = b;
@@ -315,14 +316,13 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
     const uint32_t n_cells = (uint32_t)(g.sb - g.sa + 1) * (uint32_t)g.nty * nseg;
     if (g.n_pairs > 0 && g.n_cells > 0) {
         // 3. emit (cell, strut position) items in edge-list order
-        if (g.n_active < kEmitFew)
-            k_cell_emit<4><<<(g.n_active + 15) / 16, 256, 0, st>>>(
-                g.active, g.n_active, g.ranges, g.sa, g.nty, (int32_t)nseg, g.toff, g.k0, g.v0,
-                g.n_cells);
-        else
-            k_cell_emit<16><<<(unsigned)(((size_t)g.n_active + 63) / 64), 256, 0, st>>>(
-                g.active, g.n_active, g.ranges, g.sa, g.nty, (int32_t)nseg, g.toff, g.k0, g.v0,
-                g.n_cells);
+        const bool few = g.n_active < kEmitFew;
+        const uint32_t per = few ? 16 : 64;                        // struts per block
+        for_launches(((uint64_t)g.n_active + per - 1) / per, 256, [&](uint64_t b0, uint32_t blocks) {
+            (few ? k_cell_emit<4> : k_cell_emit<16>)<<<blocks, 256, 0, st>>>(
+                (uint32_t)b0, g.active, g.n_active, g.ranges, g.sa, g.nty, (int32_t)nseg, g.toff,
+                g.k0, g.v0, g.n_cells);
+        });
         LSL_HIP(hipGetLastError());
         // 4. stable sort by cell, and the cells' CSR
         int which = 0;
@@ -359,7 +359,9 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
 
 lsl_status group_emi(const EmiArgs& a, hipStream_t st) {
     if (a.n_pairs && a.n_buckets) {
-        k_expand_keys<<<(a.n_buckets + 3) / 4, 256, 0, st>>>(a.offsets, a.n_buckets, a.keys);
+        for_launches(((uint64_t)a.n_buckets + 3) / 4, 256, [&](uint64_t block0, uint32_t blocks) {
+            k_expand_keys<<<blocks, 256, 0, st>>>((uint32_t)block0, a.offsets, a.n_buckets, a.keys);
+        });
         LSL_HIP(hipGetLastError());
     }
     if (a.n_active) k_inverse<<<(a.n_active + 255) / 256, 256, 0, st>>>(a.active, a.n_active, a.inv);
