@@ -50,7 +50,7 @@ KERNEL_SOURCES = {
     "field": ["field_q32.hpp", "field_block.hpp", "field.hip", "common.hpp", "kernels.hpp"],
     "backward": ["backward.hip", "field_q32.hpp", "grid.hpp", "common.hpp", "kernels.hpp"],
     "binning": ["prep.hip", "bin.hip", "primitives.hip", "grid.hpp", "common.hpp", "kernels.hpp"],
-    "contours": ["contours.hip", "grid.hpp", "common.hpp", "kernels.hpp"],
+    "contours": ["contours.hip", "grid.hpp", "splitters.hpp", "common.hpp", "kernels.hpp"],
 }
 
 

@@ -32,6 +32,7 @@
 
 #include "grid.hpp"
 #include "kernels.hpp"
+#include "splitters.hpp"
 
 namespace lsl {
 namespace {
@@ -447,10 +448,11 @@ __global__ __launch_bounds__(256) void k_bits_rows(const uint64_t* img, uint64_t
 // Chains and ranks.  Jumping pointers over all segments costs a pass over
 // the whole list per round (two sets of 1 + log2(longest) rounds), so only
 // splitters take part: chain starts, segments smaller than both neighbours
-// (so every closed loop has one, its smallest segment among them) and one
-// segment in kSplit by a hash of its index.
-//   1. Each splitter walks to the next one, kSplit steps on average; the
-//      segments it passes learn it and their distance from it.
+// (so every closed loop has one, its smallest segment among them) and about one
+// segment in kSplit by its index (splitters.hpp).
+//   1. Each splitter walks to the next one, kSplit steps on average along a
+//      chain of scattered indices; the segments it passes learn it and their
+//      distance from it.
 //   2. Jumping among the splitters: X is the splitter 2^r further on (or the
 //      chain's last), dX the distance to it, M the smallest segment index
 //      among the next 2^r splitters (-1 once they run past the end of an open
@@ -466,7 +468,6 @@ __global__ __launch_bounds__(256) void k_bits_rows(const uint64_t* img, uint64_t
 // no result depends on it).  Bound by gathers over the list: 5.7M segments in
 // 32 planes (1.2M splitters, loops of up to 10^5 segments) take 0.49 ms for
 // steps 1-3, against 1.76 ms for 2 x 17 rounds over all segments.
-constexpr uint32_t kSplit = 8;
 constexpr uint32_t kSuccMask = 0x3fffffffu;        // fewer than 2^30 segments
 constexpr uint32_t kSuccNone = 0x80000000u;        // end of an open chain
 constexpr uint32_t kSuccSplit = 0x40000000u;       // the successor is a splitter
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(256) void k_poly_succ(const int64_t* off, int32_t n
 __device__ __forceinline__ bool is_splitter(int32_t s, int32_t before, int32_t after) {
     if (before < 0) return true;
     if (after >= 0 && s < before && s < after) return true;
-    return (uint32_t)s * 2654435761u < 0xffffffffu / kSplit;
+    return split_pick((uint32_t)s);
 }
 
 // Numbers the splitters (own = {number, 0}, seg = their segments) and marks
@@ -758,15 +759,6 @@ size_t contour_tmp_elems(int32_t nk, int32_t W, int32_t H) {
 
 namespace {
 constexpr int32_t kPolyRounds = 32;
-
-// At most this many splitters: half of the segments are smaller than both
-// neighbours, one in kSplit is picked by the hash (which spreads consecutive
-// indices evenly, to within a few dozen), and an open chain starts on a border edge.
-uint32_t poly_splitters(uint64_t total, int32_t nk, int32_t W, int32_t H) {
-    const uint64_t border = 2 * (uint64_t)nk * ((uint64_t)W + (uint64_t)H);
-    return (uint32_t)std::min<uint64_t>(total,
-                                        total / 2 + total / kSplit + total / 64 + 1024 + border);
-}
 
 // Scratch of slice_polylines, 16-byte aligned parts.  The links and the
 // splitters' segments take the place of the emit pass's edge lists, which

@@ -139,3 +139,25 @@ def test_chains_of_every_shape(pattern, W, H, nk):
     segs, off, chain, rank = api.slice_polylines(b, field)
     if len(segs):
         check_planes(lat, field, segs, off, chain, rank, pattern)
+
+
+@pytest.mark.parametrize("walls,H", [(86, 700), (88, 700), (144, 701), (234, 300), (610, 2000)])
+def test_walls_a_constant_stride_apart(walls, H):
+    """Bars of one pixel: every row holds one segment of each wall, so a wall's
+    segments lie `walls` places apart in the list (144 and 610 are strides that a
+    multiple of the golden ratio, reduced, meets rarely).  Each wall is one open chain, up or down the plane."""
+    W = walls + 5
+    i = np.arange(W)
+    row = np.where((i % 2 == 1) & (i < walls), 1.5, 0.5).astype(np.float32)
+    lat, _ = small_kuhn()
+    b = bin_lattice(lat, synth.Grid(0.0, 0.0, 1.0, 1.0, W, H, 0.0, 1.0, 1))
+    f = torch.from_numpy(np.broadcast_to(row, (1, H, W)).copy()).cuda()
+    segs, off, chain, rank = api.slice_polylines(b, f)
+    assert off.cpu().tolist() == [0, walls * (H - 1)]
+    segs = segs.cpu().numpy().reshape(H - 1, walls, 4)
+    up = segs[..., 3] > segs[..., 1]
+    assert np.array_equal(up, np.broadcast_to(up[0], up.shape)) and 0 < up[0].sum() < walls
+    r, j = np.mgrid[0:H - 1, 0:walls]
+    assert np.array_equal(rank.cpu().numpy().reshape(r.shape), np.where(up, r, H - 2 - r))
+    assert np.array_equal(chain.cpu().numpy().reshape(r.shape),
+                          np.where(up, j, (H - 2) * walls + j))

@@ -109,7 +109,56 @@ def test_launches_cover_a_grid(tmp_path):
             return 0;
         }
     """)
-    exe = tmp_path / "grid"
-    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2101_05031_amd", "csrc"),
-                    str(src), "-o", str(exe)], check=True)
-    subprocess.run([str(exe)], check=True)
+    run_cpp(src)
+
+
+def run_cpp(src):
+    """Compiles and runs a C++ program that includes the library's host headers."""
+    exe = src.with_suffix("")
+    subprocess.run(["g++", "-O3", "-march=native", "-std=c++17", "-I",
+                    os.path.join(ROOT, "paper_2101_05031_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+def test_splitters_are_few_and_close(tmp_path):
+    """csrc/splitters.hpp: the picks never outnumber their share of the scratch
+    (all prefixes up to 2^30 segments), and along any constant stride of up to
+    2^17 segments per row the walk between two picks stays short (a wave walks as
+    long as its longest lane).  400 steps without a pick have a probability of
+    (15/16)^400 = 6e-12 under the mixed half alone; 2^28 steps are looked at."""
+    src = tmp_path / "split.cpp"
+    src.write_text("""
+        #include "splitters.hpp"
+        #include <cstdio>
+        int main() {
+            int64_t count = 0, most = 0;
+            for (uint32_t t = 0; t < (1u << 30); t += 4096) {      // the excess over t / 8
+                uint32_t c = 0;
+                for (uint32_t s = t; s < t + 4096; ++s) c += lsl::split_pick(s);
+                // (within a block of 4096 the count grows by at most all of it)
+                if (count + c - (int64_t)t / 8 > 64)
+                    for (uint32_t s = t; s < t + 4096; ++s) {
+                        count += lsl::split_pick(s);
+                        most = std::max(most, count - (int64_t)(s + 1) / 8);
+                    }
+                else
+                    count += c;
+            }
+            std::printf("excess %lld\\n", (long long)most);
+            if (most > 64) return 1;
+            uint32_t longest = 0, at = 0;
+            for (uint32_t m = 1; m <= (1u << 17); ++m) {
+                uint32_t s = 12345u + 7919u * m, last = 0;
+                for (uint32_t k = 1; k <= 2048; ++k, s += m)
+                    if (lsl::split_pick(s) || k == 2048) {
+                        if (k - last > longest) longest = k - last, at = m;
+                        last = k;
+                    }
+            }
+            std::printf("longest walk %u, stride %u\\n", longest, at);
+            return longest > 400;
+        }
+    """)
+    run_cpp(src)
