@@ -300,7 +300,7 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
         const size_t nb = (n_cand + kCTile - 1) / kCTile;
         k_active_count<<<(unsigned)nb, kCThreads, 0, st>>>(g.prev_active, g.n_prev, g.range_lo,
                                                            n_cand, g.ranges, g.sa, g.blk);
-        LSL_TRY(exclusive_scan_u32(g.blk, g.blk, nb, g.tmp, nullptr, st));
+        LSL_TRY(exclusive_scan_u32(g.blk, g.blk, nb, g.tmp, st));
         k_active_write<<<(unsigned)nb, kCThreads, 0, st>>>(g.prev_active, g.n_prev, g.range_lo,
                                                            n_cand, g.ranges, g.sa, g.blk,
                                                            g.active, g.n_active);
@@ -311,7 +311,7 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
     (all ? k_pair_counts<true> : k_pair_counts<false>)<<<(g.n_active + 1 + 255) / 256, 256, 0, st>>>(
         g.active, g.n_active, g.ranges, g.sa, g.sb, g.eoff, g.toff);
     LSL_HIP(hipGetLastError());
-    LSL_TRY(exclusive_scan_u32(g.eoff, g.eoff, (size_t)g.n_active + 1, g.tmp, nullptr, st, g.toff));
+    LSL_TRY(exclusive_scan_u32(g.eoff, g.eoff, (size_t)g.n_active + 1, g.tmp, st, g.toff));
     const uint32_t nseg = (uint32_t)((g.ntx + kSegTiles - 1) / kSegTiles);
     const uint32_t n_cells = (uint32_t)(g.sb - g.sa + 1) * (uint32_t)g.nty * nseg;
     if (g.n_pairs > 0 && g.n_cells > 0) {
@@ -339,8 +339,7 @@ lsl_status bin_group(const GroupBuffers& g, hipStream_t st) {
                                                   (int32_t)nseg, g.offsets, nullptr, nullptr, 0u);
         LSL_HIP(hipGetLastError());
         // (the count pass also clears the place after the last bucket)
-        LSL_TRY(exclusive_scan_u32(g.offsets, g.offsets, (size_t)g.n_buckets + 1, g.tmp, nullptr,
-                                   st));
+        LSL_TRY(exclusive_scan_u32(g.offsets, g.offsets, (size_t)g.n_buckets + 1, g.tmp, st));
         // 6. the bucket lists, into the buffers not holding the sorted cells
         uint32_t* ids = which ? g.v0 : g.v1;
         k_cell_buckets<true><<<gr, 256, 0, st>>>(g.roffs, cv, g.ranges, n_cells, g.ntx,

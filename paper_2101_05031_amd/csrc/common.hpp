@@ -122,16 +122,14 @@ const char* last_error();
 // Primitives (primitives.hip)
 // ---------------------------------------------------------------------------
 // Exclusive prefix sum of n values; out may alias in.  tmp must hold
-// scan_tmp_elems(n) elements of the same type.  Writes the total to
-// *total_dev when non-null.
+// scan_tmp_elems(n) elements of the same type.
 size_t scan_tmp_elems(size_t n);
 // also: a second array of n values, scanned in place by the same launches (tmp
 // then holds twice as many elements).
-lsl_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, size_t n,
-                              uint32_t* tmp, uint32_t* total_dev, hipStream_t st,
-                              uint32_t* also = nullptr);
-lsl_status exclusive_scan_u64(const uint64_t* in, uint64_t* out, size_t n,
-                              uint64_t* tmp, uint64_t* total_dev, hipStream_t st);
+lsl_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, size_t n, uint32_t* tmp,
+                              hipStream_t st, uint32_t* also = nullptr);
+lsl_status exclusive_scan_u64(const uint64_t* in, uint64_t* out, size_t n, uint64_t* tmp,
+                              hipStream_t st);
 
 // Which launches a scan or sort of n items makes (graphs of one form differ in
 // their arguments only).
@@ -160,6 +158,5 @@ lsl_status radix_sort_places(const uint32_t* keys, uint32_t* k0, uint32_t* v0, u
 
 lsl_status fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 lsl_status fill_bytes0(void* p, size_t bytes, hipStream_t st);
-lsl_status iota_u32(uint32_t* p, uint32_t base, size_t n, hipStream_t st);
 
 }  // namespace lsl

@@ -45,11 +45,10 @@ size_t strip_chunks(int32_t W) { return (size_t)(((W + 7) / 8 + kWave - 1) / kWa
 constexpr uint64_t kCol0 = 0x0101010101010101ull;   // column 0 of every row
 constexpr uint64_t kCol7 = 0x8080808080808080ull;   // column 7 of every row
 
-// Per case: number of segments and up to two segments as
-// (x0, y0, x1, y1) in half units of the cell.  The tables are folded at
-// compile time into register constants (kSegCountBits, kSegWord), so a
-// lane's lookup by its own case is arithmetic, not a memory load.
-constexpr int8_t kSegCountT[16] = {0, 1, 1, 1, 1, 2, 1, 1, 1, 1, 2, 1, 1, 1, 1, 0};
+// Per case: up to two segments (5 and 10 have two, 0 and 15 none) as
+// (x0, y0, x1, y1) in half units of the cell.  The table is folded at
+// compile time into register constants (kSegWord), so a lane's lookup by its
+// own case is arithmetic, not a memory load.
 // edge midpoints in half units: B=(1,0) E=(2,1) T=(1,2) L=(0,1)
 constexpr int8_t kSegT[16][2][4] = {
     {{0, 0, 0, 0}, {0, 0, 0, 0}},
@@ -70,12 +69,6 @@ constexpr int8_t kSegT[16][2][4] = {
     {{0, 0, 0, 0}, {0, 0, 0, 0}},
 };
 
-// 2 bits per case: the segment count
-constexpr uint32_t seg_count_bits() {
-    uint32_t r = 0;
-    for (int c = 0; c < 16; ++c) r |= (uint32_t)kSegCountT[c] << (2 * c);
-    return r;
-}
 // cases 4w .. 4w+3, 16 bits each: segment s in bits 8s .. 8s+7, its
 // coordinates (each 0, 1 or 2) in 2 bits apiece, x0 lowest
 constexpr uint64_t seg_word(int w) {
@@ -86,10 +79,7 @@ constexpr uint64_t seg_word(int w) {
                 r |= (uint64_t)kSegT[4 * w + c][s][e] << (16 * c + 8 * s + 2 * e);
     return r;
 }
-constexpr uint32_t kSegCountBits = seg_count_bits();
 constexpr uint64_t kSegWord[4] = {seg_word(0), seg_word(1), seg_word(2), seg_word(3)};
-
-__device__ __forceinline__ int seg_count(int cs) { return (int)((kSegCountBits >> (2 * cs)) & 3u); }
 
 // segment s of case cs as (x0, y0, x1, y1) in half units
 __device__ __forceinline__ void seg_points(int cs, int s, int8_t g[4]) {
@@ -851,7 +841,7 @@ lsl_status launch_contours_count(const uint64_t* img, int32_t nk, int32_t W, int
     // exclusive scan over n + 1 entries: the last one receives the total
     LSL_TRY(fill_bytes0(tot + n, 8, st));
     LSL_TRY(exclusive_scan_u64((const uint64_t*)tot, (uint64_t*)tot, n + 1, (uint64_t*)stmp,
-                               nullptr, st));
+                               st));
     k_ms_offsets<<<(nk + 1 + 255) / 256, 256, 0, st>>>(tot, nby, nk, base, offsets);
     LSL_HIP(hipGetLastError());
     return LSL_OK;

@@ -375,10 +375,6 @@ lsl_status density_plan(int32_t nk, int32_t W, int32_t H, int32_t vx, int32_t vy
     return LSL_OK;
 }
 
-size_t density_voxels(const DensityArgs& a) {
-    return (size_t)a.nx * (size_t)a.ny * (size_t)a.nz;
-}
-
 size_t density_scratch_elems(const DensityArgs& a) { return a.n_blocks; }
 
 lsl_status launch_density(int dtype, const DensityArgs& a, const void* field, double C,

@@ -319,7 +319,6 @@ struct DensityArgs {
 };
 lsl_status density_plan(int32_t nk, int32_t W, int32_t H, int32_t vx, int32_t vy, int32_t vz,
                         DensityArgs* a);
-size_t density_voxels(const DensityArgs& a);
 // doubles: per-block partial losses [n_blocks]
 size_t density_scratch_elems(const DensityArgs& a);
 lsl_status launch_density(int dtype, const DensityArgs& a, const void* field, double C,

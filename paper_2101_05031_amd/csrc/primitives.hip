@@ -115,8 +115,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const T* in, size_
 // Single block: exclusive scan of n values, carry across chunks (in may be
 // out).
 template <typename T>
-__global__ __launch_bounds__(kScanThreads) void k_scan_one(const T* in, T* out, size_t n, T* total,
-                                                           T* also, size_t also_step) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_one(const T* in, T* out, size_t n, T* also,
+                                                           size_t also_step) {
     __shared__ T sm[4];
     if (blockIdx.y) in = out = also ? also : out + also_step;
     T carry = 0;
@@ -129,7 +129,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_one(const T* in, T* out, 
         store_run(out, base, n, pre, v);
         carry += tot;
     }
-    if (threadIdx.x == 0 && total) *total = carry;
 }
 
 // The scan of one tile.  RAW: sums holds the tiles' plain totals, and the
@@ -137,7 +136,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_one(const T* in, T* out, 
 // launch of their own); else they have been scanned.
 template <typename T, bool RAW>
 __global__ __launch_bounds__(kScanThreads) void k_scan_down(const T* in, T* out, size_t n,
-                                                            const T* sums, T* total, T* also) {
+                                                            const T* sums, T* also) {
     __shared__ T sm[4];
     if (blockIdx.y) {
         in = out = also;
@@ -157,8 +156,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const T* in, T* out,
     T tot;
     const T pre = block_exclusive_scan(s, sm, &tot) + before;
     store_run(out, base, n, pre, v);
-    if (total && threadIdx.x == 0 && blockIdx.y == 0 && blockIdx.x == gridDim.x - 1)
-        *total = before + tot;
 }
 
 // Up to kScanOne values take one block (its chunks are serial, about 1 us
@@ -169,22 +166,21 @@ constexpr size_t kScanOne = 4 * (size_t)kScanTile;
 constexpr size_t kScanRaw = 4096;
 
 template <typename T>
-lsl_status scan_impl(const T* in, T* out, size_t n, T* tmp, T* total, hipStream_t st, T* also) {
+lsl_status scan_impl(const T* in, T* out, size_t n, T* tmp, hipStream_t st, T* also) {
     const size_t nb = (n + kScanTile - 1) / kScanTile;
     const unsigned na = also ? 2u : 1u;
     if (n <= kScanOne) {
-        if (n > 0 || total)
-            k_scan_one<T><<<dim3(1, na), kScanThreads, 0, st>>>(in, out, n, total, also, 0);
+        if (n > 0) k_scan_one<T><<<dim3(1, na), kScanThreads, 0, st>>>(in, out, n, also, 0);
         LSL_HIP(hipGetLastError());
         return LSL_OK;
     }
     const dim3 grid((unsigned)nb, na);
     k_scan_reduce<T><<<grid, dim3(kScanThreads), 0, st>>>(in, n, tmp, also);
     if (nb <= kScanRaw) {
-        k_scan_down<T, true><<<grid, dim3(kScanThreads), 0, st>>>(in, out, n, tmp, total, also);
+        k_scan_down<T, true><<<grid, dim3(kScanThreads), 0, st>>>(in, out, n, tmp, also);
     } else {
-        k_scan_one<T><<<dim3(1, na), kScanThreads, 0, st>>>(tmp, tmp, nb, nullptr, nullptr, nb);
-        k_scan_down<T, false><<<grid, dim3(kScanThreads), 0, st>>>(in, out, n, tmp, total, also);
+        k_scan_one<T><<<dim3(1, na), kScanThreads, 0, st>>>(tmp, tmp, nb, nullptr, nb);
+        k_scan_down<T, false><<<grid, dim3(kScanThreads), 0, st>>>(in, out, n, tmp, also);
     }
     LSL_HIP(hipGetLastError());
     return LSL_OK;
@@ -472,12 +468,6 @@ __global__ void k_fill_bytes0(uint8_t* p, size_t n) {
         p[i] = 0;
 }
 
-__global__ void k_iota_u32(uint32_t* p, uint32_t base, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (size_t)gridDim.x * blockDim.x)
-        p[i] = base + (uint32_t)i;
-}
-
 unsigned grid_for(size_t n, unsigned threads) {
     size_t g = (n + threads - 1) / threads;
     if (g > 65536u * 4u) g = 65536u * 4u;
@@ -499,13 +489,13 @@ int radix_form(size_t n) {
 size_t scan_tmp_elems(size_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
 lsl_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, size_t n, uint32_t* tmp,
-                              uint32_t* total, hipStream_t st, uint32_t* also) {
-    return scan_impl<uint32_t>(in, out, n, tmp, total, st, also);
+                              hipStream_t st, uint32_t* also) {
+    return scan_impl<uint32_t>(in, out, n, tmp, st, also);
 }
 
 lsl_status exclusive_scan_u64(const uint64_t* in, uint64_t* out, size_t n, uint64_t* tmp,
-                              uint64_t* total, hipStream_t st) {
-    return scan_impl<uint64_t>(in, out, n, tmp, total, st, nullptr);
+                              hipStream_t st) {
+    return scan_impl<uint64_t>(in, out, n, tmp, st, nullptr);
 }
 
 size_t radix_tmp_elems(size_t n) {
@@ -609,13 +599,6 @@ lsl_status fill_bytes0(void* p, size_t bytes, hipStream_t st) {
     if (bytes % 4 == 0 && ((uintptr_t)p % 4) == 0)
         return fill_u32((uint32_t*)p, 0u, bytes / 4, st);
     k_fill_bytes0<<<grid_for(bytes, 256), 256, 0, st>>>((uint8_t*)p, bytes);
-    LSL_HIP(hipGetLastError());
-    return LSL_OK;
-}
-
-lsl_status iota_u32(uint32_t* p, uint32_t base, size_t n, hipStream_t st) {
-    if (n == 0) return LSL_OK;
-    k_iota_u32<<<grid_for(n, 256), 256, 0, st>>>(p, base, n);
     LSL_HIP(hipGetLastError());
     return LSL_OK;
 }
