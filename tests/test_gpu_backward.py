@@ -333,3 +333,27 @@ def test_node_gradient_error_of_coarse_and_fine_pixels(pixel, pitch, measured):
         err.append(np.linalg.norm(gn.cpu().numpy() - rn) / np.linalg.norm(rn))
     print(f"pixel {pixel} R: node gradients' error {np.mean(err):.3e}", flush=True)
     assert np.mean(err) <= 1.05 * measured
+
+
+# The adjoint's forms: float32 with shared reference planes (pitch 0.05 R), with every
+# plane its own (0.5 R; longer slabs in windows of four planes) and with 8x8 regions
+# (pixels of 0.3 R), and float64; for each the kernels of 1, 2, 4 and 8 planes,
+# slabs that they do not divide, and planes left over at the end.
+@pytest.mark.parametrize("slab", [1, 2, 3, 4, 5, 8, 16])
+@pytest.mark.parametrize("pixel,pitch,dtype", [(0.08, 0.05, np.float32), (0.08, 0.5, np.float32),
+                                               (0.3, 0.3, np.float32), (0.3, 0.3, np.float64)])
+def test_backward_forms_and_slabs(pixel, pitch, dtype, slab):
+    lat = synth.kuhn_lattice(2, 5.0, seed=34, dtype=dtype)
+    d = pixel * lat.R
+    W = int((5.0 + 2 * lat.R) / d) + 4
+    grid = synth.Grid(-lat.R - 2 * d, -lat.R - 2 * d, d, d, W, W - 1, 1.0, pitch * lat.R, 21)
+    G = np.random.default_rng(6).normal(size=(19, grid.H, grid.W)).astype(dtype)
+    rw, rn = OG.slice_vjp(lat.nodes, lat.edges, lat.weight, lat.R, grid, range(1, 20), G)
+    for tile in (16, 64):
+        print(f"pixel {pixel} R pitch {pitch} R {np.dtype(dtype).name} slab {slab} tile {tile}",
+              flush=True)
+        b = bin_lattice(lat, grid, tile=tile, slab=slab)
+        gw, gn = api.slice_field_backward(b, 1, 19, torch.from_numpy(G).cuda())
+        rtol = 1e-4 if dtype == np.float32 else 1e-10
+        grad_close(gw.cpu().numpy(), rw, rtol, "dL/dr")
+        grad_close(gn.cpu().numpy(), rn, rtol, "dL/dv")

@@ -195,3 +195,39 @@ def test_occupancy_loss_matches_oracle(dtype):
     lv, _, gv = api.slice_density_loss(b, f, torch.from_numpy(t.astype(np.float32)).cuda(), 0.05,
                                        1, 1, 1)
     assert lv.item() == pytest.approx(rl, rel=1e-5)         # (float32 targets there)
+
+
+# 16-byte loads where field, target and gradient are all aligned, single values
+# where any is not; the last values of the aligned form; one load's worth (the
+# smallest grid has 2 x 2 pixels)
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("shift", [(0, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 1, 1), (2, 3, 1)])
+@pytest.mark.parametrize("nk,H,W", [(1, 2, 2), (1, 2, 3), (1, 3, 3), (3, 7, 11), (5, 283, 301),
+                                    (3, 1021, 1027)])
+def test_occupancy_loss_of_any_length_and_alignment(nk, H, W, shift, dtype):
+    from oracle import gradient as OG
+    lat = synth.kuhn_lattice(2, 6.0, seed=1, dtype=dtype)
+    b = bin_lattice(lat, synth.Grid(0.0, 0.0, 0.1, 0.1, W, H, 0.0, 0.1, nk))
+    n, rng = nk * H * W, np.random.default_rng(W)
+    C, torch_dtype = c_in(lat, dtype), torch.float32 if dtype == np.float32 else torch.float64
+
+    def view(values, at):
+        buf = torch.full((n + 8,), 7.0, dtype=torch_dtype, device="cuda")
+        buf[at:at + n] = torch.from_numpy(values).cuda().reshape(-1)
+        return buf, buf[at:at + n].view(nk, H, W)
+
+    f = rng.normal(1.0, 0.1, size=(nk, H, W)).astype(dtype)
+    t = rng.uniform(0.0, 1.0, size=(nk, H, W)).astype(dtype)
+    _, fv = view(f, shift[0])
+    _, tv = view(t, shift[1])
+    gbuf, gv = view(np.zeros_like(f), shift[2])
+    loss, _ = api.slice_occupancy_loss(b, fv, tv, 0.05, grad_field=gv)
+    f64, t64 = f.astype(np.float64), t.astype(np.float64)
+    rg = OG.soft_occupancy_grad(f64, t64, C, 0.05)
+    f32 = dtype == np.float32
+    assert loss.item() == pytest.approx(OG.soft_occupancy_loss(f64, t64, C, 0.05),
+                                        rel=1e-5 if f32 else 1e-12)
+    gh = gv.cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(gh - rg)) <= (1e-4 if f32 else 1e-10) * np.abs(rg).max()
+    around = torch.cat([gbuf[:shift[2]], gbuf[shift[2] + n:]])
+    assert torch.equal(around, torch.full_like(around, 7.0))
