@@ -135,9 +135,10 @@ typedef struct lsl_bins_info {
                                of an 8x8 block from its centre, R the smallest
                                support), else 1; 1 for other kernels          */
     double last_backward_ms;    /* device time of the adjoint kernels of the last
-                                   slice_field_backward call (HIP events around
-                                   them on its stream, waited for here); -1 if
-                                   none                                        */
+                                   slice_field_backward call and of the work
+                                   queues they take their items from (HIP events
+                                   around them on its stream, waited for here);
+                                   -1 if none                                  */
 } lsl_bins_info;
 
 /* ---------------------------------------------------------------------------

@@ -1653,11 +1653,6 @@ lsl_status slice_field_backward(lattice_bins* b, int32_t k0, int32_t nk, const v
             }
             BackArgs a = back_args(b, g, k0, nk, s_lo, s_hi, grad_field);
             LSL_TRY(ensure_queue(b, st));
-            FieldArgs fa = field_args(b, k0, nk, nullptr);
-            fa.group_s0 = G.sa;
-            fa.s_lo = s_lo;
-            fa.s_hi = s_hi;
-            LSL_TRY(build_queue(b, fa, &a.queue, st));
             if (b->back_events.size() <= b->n_back) {
                 lattice_bins::EvPair bp{};
                 for (auto& e : bp.ev) LSL_HIP(hipEventCreate(&e));
@@ -1665,6 +1660,11 @@ lsl_status slice_field_backward(lattice_bins* b, int32_t k0, int32_t nk, const v
             }
             hipEvent_t* bev = b->back_events[b->n_back++].ev;
             LSL_HIP(hipEventRecord(bev[0], st));
+            FieldArgs fa = field_args(b, k0, nk, nullptr);
+            fa.group_s0 = G.sa;
+            fa.s_lo = s_lo;
+            fa.s_hi = s_hi;
+            LSL_TRY(build_queue(b, fa, &a.queue, st));
             LSL_TRY(launch_backward(b->dtype, a, st));
             LSL_HIP(hipEventRecord(bev[1], st));
             ReduceArgs r{};
