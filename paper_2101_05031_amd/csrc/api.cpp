@@ -9,7 +9,9 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -161,11 +163,7 @@ class PinnedPool {
     void* take() {
         {
             std::lock_guard<std::mutex> lk(mu_);
-            if (!free_.empty()) {
-                void* p = free_.back();
-                free_.pop_back();
-                return p;
-            }
+            if (n_ > 0) return free_[--n_];
         }
         void* p = nullptr;
         if (hipHostMalloc(&p, kBytes, hipHostMallocPortable) != hipSuccess) {
@@ -177,8 +175,8 @@ class PinnedPool {
     void give(void* p) {
         {
             std::lock_guard<std::mutex> lk(mu_);
-            if (free_.size() < kKeep) {
-                free_.push_back(p);
+            if (n_ < kKeep) {
+                free_[n_++] = p;
                 return;
             }
         }
@@ -186,13 +184,14 @@ class PinnedPool {
     }
     void trim() {
         std::lock_guard<std::mutex> lk(mu_);
-        for (void* p : free_) hipHostFree(p);
-        free_.clear();
+        for (size_t i = 0; i < n_; ++i) hipHostFree(free_[i]);
+        n_ = 0;
     }
 
   private:
     std::mutex mu_;
-    std::vector<void*> free_;
+    void* free_[kKeep];
+    size_t n_ = 0;
 };
 
 // Host memory for one read-back, for the length of a call.  The copies into
@@ -201,15 +200,19 @@ class PinnedPool {
 struct HostBuf {
     void* p = nullptr;
     bool pinned = false;
-    std::vector<unsigned char> heap;
+    std::unique_ptr<unsigned char[]> heap;
     hipStream_t wait = nullptr;
     bool pending = false;
     lsl_status get(size_t bytes) {
         if (bytes <= PinnedPool::kBytes) p = PinnedPool::get().take();
         pinned = p != nullptr;
         if (!pinned) {
-            heap.resize(bytes);
-            p = heap.data();
+            heap.reset(new (std::nothrow) unsigned char[bytes]);
+            p = heap.get();
+            if (!p) {
+                set_error("host allocation of " + std::to_string(bytes) + " bytes failed");
+                return LSL_ENOMEM;
+            }
         }
         return LSL_OK;
     }
