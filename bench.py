@@ -333,8 +333,9 @@ def main():
                 "density_ms": d_ms,
                 "density_GBps": (fbytes + 4 * nvox) / (d_ms * 1e-3) / 1e9,
                 "loss_grad_ms": l_ms,
-                # two reads of the field, one write of dL/dg, voxel-sized arrays
-                "loss_grad_GBps": (3 * fbytes + 24 * nvox) / (l_ms * 1e-3) / 1e9,
+                # one read of the field and one write of dL/dg (the second read
+                # of a block's box comes from cache), target and soft density
+                "loss_grad_GBps": (2 * fbytes + 8 * nvox) / (l_ms * 1e-3) / 1e9,
                 "mean_density": float(dvox.mean())}
         del bb, dgrad, dvox
         print(f"[bench] density {d_ms:.2f} ms, loss+grad {l_ms:.2f} ms", file=sys.stderr,

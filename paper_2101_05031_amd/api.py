@@ -292,8 +292,10 @@ def slice_field_backward(bins: Bins, k0: int, nk: int, grad_field, grad_weight=N
 
 def slice_batch(bins: Bins, k0: int, nk: int, field=None, bits=None, capacity: int = 0,
                 segs=None, offsets=None, stream=None):
-    """Persistent, graph-captured slicing of planes [k0, k0+nk): returns
-    (status, total segments, segs, offsets)."""
+    """Field, binary image and contours of planes [k0, k0+nk), items in
+    descending cost order; several slab groups run through cached graphs, one
+    group as direct launches.  Returns (status, total segments, segs,
+    offsets)."""
     if offsets is None:
         offsets = torch.empty(nk + 1, dtype=torch.int64, device="cuda")
     if segs is None and capacity > 0:

@@ -430,7 +430,8 @@ struct lattice_bins {
     size_t cbits_elems = 0;
     uint32_t* pscratch = nullptr;     // slice_polylines: edges, cells, links, jumps
     size_t pscratch_elems = 0;
-    double* dscratch = nullptr;       // slice_density_loss: residuals, block partials
+    double* dscratch = nullptr;       // per-block sums of slice_density_loss and
+                                      // slice_occupancy_loss
     size_t dscratch_elems = 0;
     uint32_t* queue_buf = nullptr;     // batched path: keys/vals/alternates + running total
     size_t queue_cap = 0;

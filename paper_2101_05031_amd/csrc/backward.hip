@@ -498,11 +498,11 @@ struct Lds<SZ, true, CH> {
 // the support: the pieces of H^ above would be large).  Mode 1 takes windows
 // of at most 4 planes: with 8 its per-plane values bring a wave to 16.6 KB of
 // LDS, so that at most 9 waves fit a compute unit (11.5 KB and 13 waves with
-// 4), and a deep window's region pre-test passes nearly every pair.  Field, loss
-// and adjoint of 64 planes of 1024^2 of 115k struts 1.6 mm apart: 2.25 -> 2.07
-// ms; the adjoint of 32 planes 0.1 mm apart, 1M struts: 2.11 -> 2.00 ms.  Mode 0, whose planes share their values,
-// is slower with 4 (4.45 -> 4.88 ms: twice the wave sums), and so is mode 2
-// (0.53 -> 0.60 ms).
+// 4), and a deep window's region pre-test passes nearly every pair.  Binning,
+// field, loss and adjoint of 64 planes of 1024^2 of 115k struts 1.6 mm apart:
+// 2.32 -> 2.09 ms.  Mode 0, whose planes share their values, is slower with 4
+// (32 planes of 2048^2 of 1M struts 4.45 -> 4.88 ms: twice the wave sums), and so
+// is mode 2 (27 planes of 1021 x 1027 0.53 -> 0.60 ms).
 template <int SZ, bool SR, int MODE>
 __global__ __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
@@ -520,7 +520,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_backward32(
     // the items in descending cost order, handed out by the hardware as others
     // end: a bucket is a long item (a few to a wave's place), and the last
     // ones to run had better be short: 27 planes of 1021 x 1027 in 16640
-    // buckets 0.70 -> 0.54 ms, 32 planes of 2048^2 in 16384 4.90 -> 4.44 ms
+    // buckets 0.70 -> 0.55 ms, 32 planes of 2048^2 in 16384 4.90 -> 4.44 ms
     uint32_t t = a.queue[item0 + blockIdx.x];
     const int tx = (int)(t % (uint32_t)a.ntx);
     t /= (uint32_t)a.ntx;
